@@ -295,12 +295,43 @@ __global__ __launch_bounds__(kBlock) void k_spectrum(const Tin* __restrict__ vol
     }
 }
 
+// Record j of a buffer range of records (nothing is stored where it is out of
+// the range).
+template <typename R>
+__device__ __forceinline__ void store_record(const R& v, __amdgpu_buffer_rsrc_t r, unsigned j)
+{
+    constexpr int W = (int)(sizeof(R) / 16);
+    struct alignas(16) Word {
+        unsigned v[4];
+    };
+    struct alignas(16) Words {
+        Word w[W];
+    };
+    const Words d = __builtin_bit_cast(Words, v);
+#pragma unroll
+    for (int i = 0; i < W; ++i) buffer_store16(d.w[i], r, j * (unsigned)sizeof(R) + 16u * i);
+}
+
 // Bins per thread the streaming spectrum kernel stores: it serves bands of at
 // most N/4 bins (30-80 MHz at 200 MHz sampling is 0.25 N bins); wider bands
 // take k_spectrum.
 constexpr int kSpecStreamBins = 2;
 
-// The same spectra by a persistent grid (FP32, 8 values per thread, radix 8):
+// The sample of the largest pw and the smallest sample on ties, over the
+// wavefront, from each lane's own (pw < 0: none; 0 if no lane has one): the
+// maximum of the high words, of the low words among those, of n_minus =
+// (last sample - sample) among those; every step is one instruction.
+__device__ __forceinline__ void wave_first_max(double pw, unsigned n_minus, unsigned& hi, unsigned& lo,
+                                               unsigned& at)
+{
+    const unsigned h = pw < 0.0 ? 0u : (unsigned)__double2hiint(pw) + 1u;
+    hi = wave_max_key(h);
+    const unsigned l = h == hi ? (unsigned)__double2loint(pw) : 0u;
+    lo = wave_max_key(l);
+    at = wave_max_key(h == hi && l == lo ? n_minus : 0u);
+}
+
+// The same spectra by a persistent grid (8 values per thread, radix 8):
 // each workgroup takes the stations blockIdx.x, blockIdx.x + gridDim.x, ...
 // and issues the trace loads of its next station before transforming the
 // current one, so that their latency hides behind the transform.  Nothing in
@@ -310,19 +341,26 @@ constexpr int kSpecStreamBins = 2;
 // pass's in registers, both set
 // once, and every thread issues a fixed number of spectrum stores, the lanes
 // past the band storing out of range of the row (dropped).
-template <typename Tin, int N>
+// TIMING: also the station's first time (k_volt_timing's result, from the
+// trace values the transform holds anyway: the reconstruction loop reads its
+// traces once instead of twice); V_0^2 + V_1^2 in double with every operation
+// rounded on its own.
+// Against k_spectrum, double precision, 124 stations x 4096 samples: 13.9 ->
+// 11.5 us; with k_volt_timing, 96 events of 3 to 124 stations x 4096 float
+// samples: 108 -> 70 us.
+template <typename Tin, typename T, int N, bool TIMING>
 __global__ __launch_bounds__(N / 8) void k_spectrum_stream(const Tin* __restrict__ volt, EvDesc ev0,
                                                            const EvDesc* __restrict__ evs,
                                                            const int2* __restrict__ units, int n_units,
-                                                           XBin<float>* __restrict__ X,
-                                                           const C2<float>* __restrict__ tw)
+                                                           XBin<T>* __restrict__ X,
+                                                           const C2<T>* __restrict__ tw, int* __restrict__ t0)
 {
-    using T = float;
-    constexpr int E = 8, RMAX = 8, TT = N / E;
+    constexpr int E = 8, RMAX = 8, TT = N / E, NW = TT / 64;
     static_assert(kSpecStreamBins * TT <= N, "gathered bins stay inside the transform");
     extern __shared__ __align__(16) unsigned char smem[];
     C2<T>* lds = reinterpret_cast<C2<T>*>(smem);
     C2<T>* ltw = lds + lds_elems<N>();
+    __shared__ unsigned first[TIMING ? 3 : 1][TIMING ? NW : 1];
     const int t = threadIdx.x;
     C2<T> w[tw_count<N, E, RMAX, TW_LF>()];
     load_twiddles<T, N, E, RMAX, TW_LF, +1>(w, tw, t);  // TW_LF entries serve both directions
@@ -365,6 +403,28 @@ __global__ __launch_bounds__(N / 8) void k_spectrum_stream(const Tin* __restrict
         C2<T> x[E];
 #pragma unroll
         for (int i = 0; i < E; ++i) x[i] = C2<T>{(T)a[i], (T)b[i]};
+        if constexpr (TIMING) {
+#pragma clang fp contract(off)
+            // this wave's part; merged after the transform's barriers
+            double bv = -1.0;
+            int bi = 0;
+#pragma unroll
+            for (int i = 0; i < E; ++i) {
+                const double va = (double)a[i], vb = (double)b[i];
+                const double pw = va * va + vb * vb;
+                if (pw > bv) {
+                    bv = pw;
+                    bi = t + TT * i;
+                }
+            }
+            unsigned hi, lo, at;
+            wave_first_max(bv, (unsigned)(N - 1 - bi), hi, lo, at);
+            if ((t & 63) == 0) {
+                first[0][t >> 6] = hi;
+                first[1][t >> 6] = lo;
+                first[2][t >> 6] = at;
+            }
+        }
         const int un = u + (int)gridDim.x;
         Row next = row;
         if (un < n_units) {
@@ -379,6 +439,17 @@ __global__ __launch_bounds__(N / 8) void k_spectrum_stream(const Tin* __restrict
 #pragma unroll
         for (int i = 0; i < E; ++i) lds[lpad<T>(t + TT * i)] = x[i];
         lds_barrier();
+        if constexpr (TIMING) {
+            // lanes past the waves hold nothing
+            if (t < 64) {
+                const unsigned h = t < NW ? first[0][t < NW ? t : 0] : 0u;
+                const unsigned hi = wave_max_key(h);
+                const unsigned l = t < NW && h == hi ? first[1][t < NW ? t : 0] : 0u;
+                const unsigned lo = wave_max_key(l);
+                const unsigned at = wave_max_key(t < NW && h == hi && l == lo ? first[2][t < NW ? t : 0] : 0u);
+                if (t == 0) t0[u] = hi == 0u ? 0 : N - 1 - (int)at;
+            }
+        }
         const unsigned nb = (unsigned)row.nb;
         const __amdgpu_buffer_rsrc_t out = buffer_range(row.out, nb * (unsigned)sizeof(XBin<T>));
 #pragma unroll
@@ -390,7 +461,7 @@ __global__ __launch_bounds__(N / 8) void k_spectrum_stream(const Tin* __restrict
             XBin<T> r;
             r.x0 = C2<T>{(T)0.5 * (za.re + zb.re), (T)0.5 * (za.im - zb.im)};
             r.x1 = C2<T>{(T)0.5 * (za.im + zb.im), (T)0.5 * (zb.re - za.re)};
-            buffer_store16(r, out, (j < nb ? j : nb) * (unsigned)sizeof(XBin<T>));
+            store_record(r, out, j < nb ? j : nb);
         }
         if (un >= n_units) break;
         // every gather done before the next transform writes the buffer
@@ -1816,42 +1887,58 @@ static int unfold_variant(int prec, int n)
     return g_variant[prec == AU_PREC_FP32 ? 1 : 0][ilog2(n)];
 }
 
+template <typename Tin>
+__global__ void k_volt_timing(const Tin* __restrict__ volt, int N, int* __restrict__ t0,
+                              const EvDesc* __restrict__ evs, const int2* __restrict__ units);
+
+// LDS of k_spectrum_stream: one transform and the early passes' twiddles.
+template <typename T, int N>
+constexpr size_t spectrum_stream_lds() { return (lds_elems<N>() + ltw_count<N, 8, 8, TW_LF>()) * sizeof(C2<T>); }
+
 // Workgroups of k_spectrum_stream the device holds at once (0 if unknown).
-template <typename Tin, int N>
+template <typename Tin, typename T, int N, bool TIMING>
 static int spectrum_stream_blocks()
 {
     static const int blocks = [] {
-        constexpr size_t lds = (lds_elems<N>() + ltw_count<N, 8, 8, TW_LF>()) * sizeof(C2<float>);
         int dev = 0, cus = 0, occ = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_spectrum_stream<Tin, N>, N / 8, lds) != hipSuccess)
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_spectrum_stream<Tin, T, N, TIMING>, N / 8,
+                                                         spectrum_stream_lds<T, N>()) != hipSuccess)
             return 0;
         return cus * occ;
     }();
     return blocks;
 }
 
-// max_nb: the largest band (bins) of the launch's events.
+// Spectra of n_units stations and, with t0, their first times (t0[unit]).
+// max_nb: the largest band (bins) of the launch's events.  The streaming
+// kernel from 512 samples up (a wavefront per transform at least) where its
+// fixed number of stores per thread covers the band.
 template <typename Tin, typename T, int N>
 static hipError_t launch_spectrum_n(hipStream_t st, const Tin* volt, const EvDesc& ev0,
                                     const EvDesc* evs, const int2* units, int n_units, int max_nb,
-                                    XBin<T>* X, const C2<T>* tw)
+                                    XBin<T>* X, const C2<T>* tw, int* t0)
 {
     using S = Shape<T, N>;
     if (n_units <= 0) return hipSuccess;
-    if constexpr (sizeof(T) == 4 && N >= 1024) {
-        const int blocks = spectrum_stream_blocks<Tin, N>();
+    if constexpr (N >= 512) {
+        const int blocks = t0 ? spectrum_stream_blocks<Tin, T, N, true>() : spectrum_stream_blocks<Tin, T, N, false>();
         if (max_nb <= kSpecStreamBins * (N / 8) && blocks > 0) {
-            constexpr size_t lds = (lds_elems<N>() + ltw_count<N, 8, 8, TW_LF>()) * sizeof(C2<float>);
-            hipLaunchKernelGGL((k_spectrum_stream<Tin, N>), dim3(std::min(n_units, blocks)), dim3(N / 8), lds,
-                               st, volt, ev0, evs, units, n_units, X, tw);
+            const dim3 grid(std::min(n_units, blocks)), block(N / 8);
+            if (t0)
+                hipLaunchKernelGGL((k_spectrum_stream<Tin, T, N, true>), grid, block, (spectrum_stream_lds<T, N>()),
+                                   st, volt, ev0, evs, units, n_units, X, tw, t0);
+            else
+                hipLaunchKernelGGL((k_spectrum_stream<Tin, T, N, false>), grid, block, (spectrum_stream_lds<T, N>()),
+                                   st, volt, ev0, evs, units, n_units, X, tw, t0);
             return hipGetLastError();
         }
     }
     const int grid = (n_units + S::G - 1) / S::G;
     hipLaunchKernelGGL((k_spectrum<Tin, T, N, S::E>), dim3(grid), dim3(S::BLOCK), S::LDS, st, volt,
                        ev0, evs, units, n_units, X, tw);
+    if (t0) hipLaunchKernelGGL(k_volt_timing<Tin>, dim3(n_units), dim3(kBlock), 0, st, volt, N, t0, evs, units);
     return hipGetLastError();
 }
 
@@ -1986,11 +2073,11 @@ static int occupancy_nv()
 template <typename Tin, typename T>
 static hipError_t launch_spectrum(int n, hipStream_t st, const Tin* volt, const EvDesc& ev0,
                                   const EvDesc* evs, const int2* units, int n_units, int max_nb,
-                                  XBin<T>* X, const C2<T>* tw)
+                                  XBin<T>* X, const C2<T>* tw, int* t0 = nullptr)
 {
     switch (n) {
 #define X_(NN) \
-    case NN: return launch_spectrum_n<Tin, T, NN>(st, volt, ev0, evs, units, n_units, max_nb, X, tw);
+    case NN: return launch_spectrum_n<Tin, T, NN>(st, volt, ev0, evs, units, n_units, max_nb, X, tw, t0);
         AU_FOR_EACH_N(X_)
 #undef X_
     }
@@ -3912,16 +3999,10 @@ static au_status run_reconstruct(const au_table* tb, const au_event* ev, const E
     const C2<T>* tw = twiddles<T>(tb->device);
     if (tw == nullptr) return fail(AU_EDEVICE, "twiddle tables missing on this device");
     hipError_t e;
-    if (ev->trace_dtype == AU_F64) {
-        e = launch_spectrum<double, T>(p.N, st, (const double*)d_volt, ev0, nullptr, nullptr, p.S, ev0.nb, X, tw);
-        hipLaunchKernelGGL(k_volt_timing<double>, dim3(p.S), dim3(kBlock), 0, st, (const double*)d_volt, p.N, hist,
-                           (const EvDesc*)nullptr, (const int2*)nullptr);
-    } else {
-        e = launch_spectrum<float, T>(p.N, st, (const float*)d_volt, ev0, nullptr, nullptr, p.S, ev0.nb, X, tw);
-        hipLaunchKernelGGL(k_volt_timing<float>, dim3(p.S), dim3(kBlock), 0, st, (const float*)d_volt, p.N, hist,
-                           (const EvDesc*)nullptr, (const int2*)nullptr);
-    }
-    if (e == hipSuccess) e = hipGetLastError();
+    if (ev->trace_dtype == AU_F64)
+        e = launch_spectrum<double, T>(p.N, st, (const double*)d_volt, ev0, nullptr, nullptr, p.S, ev0.nb, X, tw, hist);
+    else
+        e = launch_spectrum<float, T>(p.N, st, (const float*)d_volt, ev0, nullptr, nullptr, p.S, ev0.nb, X, tw, hist);
     if (e != hipSuccess) return fail(AU_EDEVICE, std::string("spectrum/timing: ") + hipGetErrorString(e));
     const double dt_ns = 1e9 / (double)ev->fs_hz;
     // The loop's launches, in order: op 2 it is step `it` (with the
@@ -4436,16 +4517,10 @@ static au_status run_reconstruct_batch(const au_table* tb, const au_event* ev, c
     const C2<T>* tw = twiddles<T>(tb->device);
     if (tw == nullptr) return fail(AU_EDEVICE, "twiddle tables missing on this device");
     hipError_t e;
-    if (ev->trace_dtype == AU_F64) {
-        e = launch_spectrum<double, T>(p.N, st, (const double*)d_volt, ev0, evs, sunits, (int)stot, p.nb, X, tw);
-        hipLaunchKernelGGL(k_volt_timing<double>, dim3((unsigned)stot), dim3(kBlock), 0, st, (const double*)d_volt,
-                           p.N, hist, (const EvDesc*)evs, (const int2*)sunits);
-    } else {
-        e = launch_spectrum<float, T>(p.N, st, (const float*)d_volt, ev0, evs, sunits, (int)stot, p.nb, X, tw);
-        hipLaunchKernelGGL(k_volt_timing<float>, dim3((unsigned)stot), dim3(kBlock), 0, st, (const float*)d_volt,
-                           p.N, hist, (const EvDesc*)evs, (const int2*)sunits);
-    }
-    if (e == hipSuccess) e = hipGetLastError();
+    if (ev->trace_dtype == AU_F64)
+        e = launch_spectrum<double, T>(p.N, st, (const double*)d_volt, ev0, evs, sunits, (int)stot, p.nb, X, tw, hist);
+    else
+        e = launch_spectrum<float, T>(p.N, st, (const float*)d_volt, ev0, evs, sunits, (int)stot, p.nb, X, tw, hist);
     if (e != hipSuccess) return fail(AU_EDEVICE, std::string("spectrum/timing: ") + hipGetErrorString(e));
     const double dt_ns = 1e9 / (double)ev->fs_hz;
     for (int it = 0; it <= max_iter; ++it) {

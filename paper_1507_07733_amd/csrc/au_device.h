@@ -1066,6 +1066,26 @@ __device__ __forceinline__ void fft4096_xw2(C2<T> (&x)[8], C2<T> (&y)[8], C2<T>*
     xw_pass<T, 512, SIGN, TWMODE>(y, w, ltw, t);
 }
 
+// Maximum of unsigned keys over the wavefront, uniform.  (DPP row shifts by 1,
+// 2, 4, 8 leave each row's maximum in its last lane, the two row broadcasts
+// carry it on to lane 63; lanes without a source take 0, which leaves their
+// own key, so that every step is one instruction.)
+template <int CTRL>
+__device__ __forceinline__ unsigned dpp_or_zero(unsigned v)
+{
+    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+}
+__device__ __forceinline__ unsigned wave_max_key(unsigned v)
+{
+    v = max(v, dpp_or_zero<0x111>(v));
+    v = max(v, dpp_or_zero<0x112>(v));
+    v = max(v, dpp_or_zero<0x114>(v));
+    v = max(v, dpp_or_zero<0x118>(v));
+    v = max(v, dpp_or_zero<0x142>(v));
+    v = max(v, dpp_or_zero<0x143>(v));
+    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+
 // Full N-point transform of the group's sequence, exp(SIGN ...) kernel, no
 // scaling.  Every thread of the group must call it; unless WAVE it contains
 // workgroup barriers, so every thread of the workgroup must call it.
