@@ -1088,6 +1088,22 @@ __device__ __forceinline__ V buffer_load_scalar(__amdgpu_buffer_rsrc_t r, unsign
     }
 }
 
+// Record j of a buffer range of records (zeros where it is out of the range).
+template <typename R>
+__device__ __forceinline__ R load_record(__amdgpu_buffer_rsrc_t r, unsigned j)
+{
+    constexpr int W = (int)(sizeof(R) / 16);
+    struct alignas(16) Word {
+        unsigned v[4];
+    };
+    struct alignas(16) Words {
+        Word w[W];
+    } d;
+#pragma unroll
+    for (int i = 0; i < W; ++i) d.w[i] = buffer_load16<Word>(r, j * (unsigned)sizeof(R) + 16u * i);
+    return __builtin_bit_cast(R, d);
+}
+
 // ---------------------------------------------------------------------------
 // Spectrum and unfold fused, for events with few directions (FP32)
 // ---------------------------------------------------------------------------
@@ -1762,6 +1778,375 @@ __global__ __launch_bounds__((N / E) > kBlock ? (N / E) : kBlock) void k_unfold_
             }
         }
         lds_barrier();
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Envelope peaks without the traces (the scan's, the loop's and the fit's
+// timing step) for bands of at most N/4 bins
+// ---------------------------------------------------------------------------
+
+// The envelope sqrt(e^2 + H(e)^2) is the magnitude of the analytic signal
+// a[n] = sum_k 2 E[k] exp(2 pi i k n / N) over the in-band bins k > 0 (its real
+// part is e, its imaginary part H(e); at k = 0 the real part of E counts
+// once), and a shift of the band to bins 0, 1, ... only turns a's phase.  So
+// the theta and phi envelopes are the magnitudes of two transforms of at most
+// N/4 consecutive bins, j = k - k_lo: qb_transform.  Against the two full
+// transforms of the packed pair and its Hilbert partner (k_unfold_env) nothing
+// is staged through LDS, since the first pass takes each thread's own two
+// bins t and t + N/8 from the registers it solved them in, six of the first
+// pass's eight inputs vanish, and the two transforms follow each other through
+// one buffer, so that twice the workgroups fit a CU.
+//
+// The sample of the maximum has to be the one that k_unfold_env takes,
+// whatever the rounding of either: where another sample comes within kEnvNear
+// of it (below), the station is evaluated again with k_unfold_env's
+// operations (env_redo), which decide.  That is a few stations in 10^5 for
+// traces with noise, and every station of a field that is zero.
+
+// Relative distance in amplitude, to the total field's maximum, within which
+// two samples may change places between the two evaluations: 2^-15 (float),
+// 2^-44 (double).  Either transform is off by at most about 2 log2(N) u of the
+// total field's largest magnitude (u = 2^-24 or 2^-53; the error observed is a
+// tenth of that), and four such errors (two samples, two evaluations) can add
+// up: 96 u at N = 4096, taken with a factor of five to spare.
+// Squares below this are decided by env_redo too: they may have lost bits to
+// underflow.
+template <typename T>
+constexpr T kEnvTiny = sizeof(T) == 4 ? (T)0x1p-100 : (T)0x1p-960;
+
+// Stations a workgroup takes between two looks at the near-tie counts.
+constexpr int kEnvRound = 32;
+
+// The maxima are taken over 32-bit keys of the squares: their bits (float) or
+// high words (double), which order squares as integers.
+__device__ __forceinline__ unsigned env_key(float v) { return __float_as_uint(v); }
+__device__ __forceinline__ unsigned env_key(double v) { return (unsigned)__double2hiint(v); }
+
+// The smallest key that counts as near the key m of a component's largest
+// square, R2 the total's: an amplitude within kEnvNear R of sqrt(m) has a square
+// above m (1 - 2 kEnvNear R / sqrt(m)); a relative step of 2^-b moves a key by
+// at most 2^(B - b) (B one more than its mantissa bits), and R / sqrt(m) is below
+// 2^((e + 2) / 2) for a difference of e in the binary exponents.
+template <typename T>
+__device__ __forceinline__ unsigned env_near_key(unsigned m, unsigned r2)
+{
+    constexpr int MB = sizeof(T) == 4 ? 23 : 20;
+    constexpr int STEP = sizeof(T) == 4 ? MB + 1 - 15 + 1 : 0;  // log2 of 2 kEnvNear 2^B (at least 1 key)
+    const int h = STEP + (((int)(r2 >> MB) - (int)(m >> MB) + 2) >> 1) - (sizeof(T) == 4 ? 0 : 22);
+    const unsigned d = h <= 0 ? 2u : (h >= 31 ? m : (1u << h) + 1u);
+    return d >= m ? 0u : m - d;
+}
+
+// Values per thread and twiddles of k_unfold_env at this length (its
+// operations are what env_redo repeats).
+template <int N>
+constexpr int env_e() { return N >= 1024 ? 8 : (N < 16 ? N : 16); }
+
+// One station's maxima of the components in `comps` (a bit each) with
+// k_unfold_env's operations: both transforms of the
+// packed spectra, one after the other through `la` (N slots), the maxima of the
+// squared envelopes decided in the same order.  Every thread of the workgroup
+// calls it, after a barrier that follows the last use of `la`.  A function of its
+// own, so that none of its registers are the caller's loop's (KERNEL: one per
+// calling kernel, which gives it its register budget).
+template <typename T, int N, int KERNEL>
+__device__ __attribute__((noinline)) void env_redo(const XBin<T>* __restrict__ Xs, const MBin<T>* __restrict__ Md, unsigned nb,
+                                         unsigned k_lo, T* __restrict__ peak, int* __restrict__ arg, unsigned comps,
+                                         C2<T>* __restrict__ la, const C2<T>* __restrict__ tw, T (*red_v)[N / 512],
+                                         int (*red_i)[N / 512])
+{
+    constexpr int TT = N / 8, E = env_e<N>(), TE = N / E, NW = N / 512;
+    constexpr int TWM = E == 8 ? TW_LFT : TW_TABLE;
+    constexpr bool WAVE = NW == 1;
+    // opaque, so that none of this path's addresses are computed ahead of the
+    // caller's loop and held in registers through it
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    for (int i = t; i < N; i += TT) la[lpad<T>(i)] = C2<T>{0, 0};
+    lds_sync<WAVE>();
+    for (unsigned j = t; j < nb; j += TT) stage_bin<T, N>(la, k_lo + j, Md[j], Xs[j]);
+    lds_sync<WAVE>();
+    C2<T> x[E], xh[E];
+    if (t < TE) {
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+            x[i] = la[lpad<T>(t + TE * i)];
+            // Zh = -i Z below N/2, i Z above, 0 at DC (Nyquist is out of band)
+            xh[i] = i < E / 2 ? C2<T>{x[i].im, -x[i].re} : C2<T>{-x[i].im, x[i].re};
+        }
+        if (t == 0) xh[0] = C2<T>{0, 0};
+    }
+    lds_sync<WAVE>();
+    T bv[3] = {(T)-1, (T)-1, (T)-1};
+    int bi[3] = {0, 0, 0};
+    if (t < TE) {  // (all threads where the transform has workgroup barriers)
+        fft<T, N, E, +1, TWM, E, WAVE>(x, la, tw, t);
+        fft<T, N, E, +1, TWM, E, WAVE>(xh, la, tw, t);
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+            const T p0 = x[i].re * x[i].re + xh[i].re * xh[i].re;
+            const T p1 = x[i].im * x[i].im + xh[i].im * xh[i].im;
+            const T e[3] = {p0, p1, p0 + p1};
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                if (e[c] > bv[c]) {
+                    bv[c] = e[c];
+                    bi[c] = t + TE * i;
+                }
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        for (int off = 32; off >= 1; off >>= 1) {
+            const T ov = __shfl_xor(bv[c], off);
+            const int oi = __shfl_xor(bi[c], off);
+            if (ov > bv[c] || (ov == bv[c] && oi < bi[c])) {
+                bv[c] = ov;
+                bi[c] = oi;
+            }
+        }
+        if ((t & 63) == 0) {
+            red_v[c][t >> 6] = bv[c];
+            red_i[c][t >> 6] = bi[c];
+        }
+    }
+    lds_sync<WAVE>();
+    if ((comps >> t) & (t < 3)) {
+        T v = red_v[t][0];
+        int ix = red_i[t][0];
+        for (int k = 1; k < NW; ++k) {
+            const T ov = red_v[t][k];
+            const int oi = red_i[t][k];
+            if (ov > v || (ov == v && oi < ix)) {
+                v = ov;
+                ix = oi;
+            }
+        }
+        peak[t] = sqrt(v);
+        arg[t] = ix;
+    }
+    lds_sync<WAVE>();
+}
+
+// The maxima of a station's squared theta (pt) and phi (pp) envelopes and their
+// sum, components c_lo .. 2 (thread t holds the samples out0 + (N/8) r).  top_key
+// and near_cnt: LDS words of the station (column `it`), zero before.  A maximum
+// with no other sample near it is stored with its sample, and near_cnt then holds
+// 1; where it ends above 1 the component is env_redo's to decide (after a
+// barrier).  Holds a barrier, which every thread passes after its last use of the
+// exchange buffer.
+template <typename T, int N, int R>
+__device__ __forceinline__ void env_maxima(const T (&pt)[8], const T (&pp)[8], int c_lo, unsigned (&top_key)[3][R],
+                                           unsigned (&near_cnt)[3][R], int it, T* __restrict__ peak,
+                                           int* __restrict__ arg, int out0, int t)
+{
+    constexpr int TT = N / 8;
+    constexpr bool WAVE = N == 512;
+    const int lane = t & 63;
+    // the keys' maxima over the thread, the wave and the workgroup
+    unsigned mine[3], top[3] = {0, 0, 0};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        if (c < c_lo) continue;
+        unsigned k[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) k[r] = env_key(c == 0 ? pt[r] : (c == 1 ? pp[r] : pt[r] + pp[r]));
+        mine[c] = max(max(max(k[0], k[1]), max(k[2], k[3])), max(max(k[4], k[5]), max(k[6], k[7])));
+        top[c] = wave_max_key(mine[c]);
+        if (!WAVE && lane == 0) atomicMax(&top_key[c][it], top[c]);
+    }
+    lds_sync<WAVE>();
+    if constexpr (!WAVE) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            if (c >= c_lo) top[c] = (unsigned)__builtin_amdgcn_readfirstlane((int)top_key[c][it]);
+    }
+    // samples near a maximum are counted
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        if (c < c_lo) continue;
+        const unsigned thr = env_near_key<T>(top[c], top[2]);
+        if (__ballot(mine[c] >= thr) == 0ull) continue;  // no lane of this wave
+        unsigned n_near = 0;
+        int at_r = 8;
+        T v_at = 0;
+#pragma unroll
+        for (int r = 7; r >= 0; --r) {
+            const T v = c == 0 ? pt[r] : (c == 1 ? pp[r] : pt[r] + pp[r]);
+            const bool near = env_key(v) >= thr;
+            n_near += (unsigned)__popcll(__ballot(near));
+            if (near) {
+                at_r = r;
+                v_at = v;
+            }
+        }
+        if (at_r < 8) {
+            peak[c] = sqrt(v_at);
+            arg[c] = out0 + TT * at_r;
+        }
+        if (lane == 0) atomicAdd(&near_cnt[c][it], n_near);
+    }
+    // not a number, infinite or tiny: all for env_redo
+    if ((top[2] < env_key(kEnvTiny<T>) || top[2] >= env_key((T)INFINITY)) && t < 3)
+        atomicAdd(&near_cnt[t][it], 2u);
+}
+
+// The bins t and t + N/8 of a row of nb, from the packed coefficients and the
+// spectra (zero past the row): 2 E_theta and 2 i E_phi; at DC (k_lo = 0) the real
+// parts of E, once.
+template <typename T, int N>
+__device__ __forceinline__ void env_bins(const MBin<T> (&mb)[2], const XBin<T> (&xb)[2], unsigned k_lo, int t,
+                                         C2<T> (&at)[2], C2<T> (&ap)[2])
+{
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        C2<T> zp, zq;
+        packed_bin(mb[k], xb[k], zp, zq);
+        at[k] = cadd(zp, zq);
+        ap[k] = csub(zp, zq);
+    }
+    if (k_lo == 0 && t == 0) {
+        at[0] = C2<T>{(T)0.5 * at[0].re, 0};
+        ap[0] = C2<T>{0, (T)0.5 * ap[0].im};
+    }
+}
+
+// Station-unfolds u in [0, n_su) are spread over the grid (a multiple of 8
+// workgroups, at most what the device holds): XCD x = block mod 8 takes the
+// x-th eighth, its workgroups stride through it side by side, so that at any
+// time an XCD works on one or two directions and their coefficient rows stay
+// in its L2.  One event: u = direction * S + station.  Many events (sunits[u] =
+// (event, station), one direction each): the peaks of u go to rows 3 u, and
+// an event whose skip flag is set is passed over.
+//
+// Bound by VALU issue: about 610 instructions per wave and station in float
+// (468 of them the two transforms, at 3 per point and radix-2 level), of which
+// the SIMDs can take one per 4 cycles.  124 stations x 4096 samples, k_unfold_env
+// against this: float, 512 directions, 830 -> 661 us; double, 2048 directions,
+// 7.36 -> 4.1 ms; 2048 samples, 87 stations x 700 directions, 352 -> 322 us and
+// 782 -> 521 us.  Registers: double 128 (4 waves per SIMD, two workgroups per
+// CU at 4096 samples); float 80 (6 waves: 734 us at 4 waves, and 64 registers
+// spill), except at 512 samples, where 4 waves measured 8 % faster.
+template <typename T, int N>
+constexpr int env_peaks_min_waves() { return sizeof(T) == 8 || N == 512 ? 4 : 6; }
+
+template <typename T, int N>
+__global__ __launch_bounds__(N / 8) __attribute__((amdgpu_waves_per_eu(env_peaks_min_waves<T, N>()))) void k_env_peaks(
+    EvDesc ev0, int64_t n_su, const XBin<T>* __restrict__ X, const MBin<T>* __restrict__ M, T* __restrict__ peak,
+    int* __restrict__ arg, const C2<T>* __restrict__ tw, const int* __restrict__ skip,
+    const EvDesc* __restrict__ evs, const int2* __restrict__ sunits, int skip_stride, int total_only)
+{
+    constexpr int TT = N / 8, NW = N / 512;
+    constexpr bool WAVE = NW == 1;
+    if (sunits == nullptr && skip != nullptr && skip[0]) return;  // set by a converged reconstruction loop
+    __shared__ C2<T> la[qb_elems<N>()];
+    __shared__ T red_v[3][NW];
+    __shared__ int red_i[3][NW];
+    __shared__ unsigned top_key[3][kEnvRound], near_cnt[3][kEnvRound];  // per station of a round
+    const int t = threadIdx.x, lane = t & 63;
+    const int c_lo = total_only ? 2 : 0;
+    QbTwiddles<T, N> q;
+    qb_load_uniform<T, N>(q, tw, t);
+    qb_load_lanes<T, N>(q, tw, t);
+    for (int i = t; i < 3 * kEnvRound; i += TT) (&near_cnt[0][0])[i] = (&top_key[0][0])[i] = 0;
+    // this workgroup's station-unfolds: u, u + step, ... below u_end
+    const int64_t xcd = blockIdx.x & 7, u_end = n_su * (xcd + 1) / 8;
+    int64_t u = n_su * xcd / 8 + (blockIdx.x >> 3);
+    const int step = (int)(gridDim.x >> 3);
+    struct Su {
+        const XBin<T>* x;
+        const MBin<T>* m;
+        unsigned nb, k_lo;
+    };
+    auto locate = [&](int64_t uu) {
+        if (sunits != nullptr) {
+            const int2 es = sunits[uu];
+            const EvDesc& e = evs[es.x];
+            return Su{X + e.x_off + (int64_t)es.y * e.nb, M + e.m_off, (unsigned)e.nb, (unsigned)e.k_lo};
+        }
+        const int64_t d = uu / ev0.S;
+        const int64_t s = uu - d * ev0.S;
+        return Su{X + s * ev0.nb, M + d * ev0.nb, (unsigned)ev0.nb, (unsigned)ev0.k_lo};
+    };
+    // (one event: the direction and station of u, stepped without a division)
+    const int S1 = max(ev0.S, 1);
+    const int d_step = step / S1, s_step = step - d_step * S1;
+    int64_t d_at = u / S1;
+    int s_at = (int)(u - d_at * S1);
+    vmem_wait_all();
+    lds_sync<WAVE>();
+    while (u < u_end) {
+        const int64_t u_first = u;
+        for (int it = 0; it < kEnvRound && u < u_end; ++it, u += step) {
+            Su su;
+            if (sunits != nullptr) {
+                if (skip != nullptr && skip[(int64_t)sunits[u].x * skip_stride]) continue;
+                su = locate(u);
+            } else {
+                su = Su{X + (int64_t)s_at * ev0.nb, M + d_at * ev0.nb, (unsigned)ev0.nb, (unsigned)ev0.k_lo};
+                d_at += d_step;
+                s_at += s_step;
+                if (s_at >= ev0.S) {
+                    s_at -= ev0.S;
+                    ++d_at;
+                }
+            }
+            // the bins t and t + N/8 (zero coefficients and spectra past the
+            // band: the loads are out of the rows' range)
+            C2<T> at[2], ap[2];
+            {
+                const __amdgpu_buffer_rsrc_t xr = buffer_range(su.x, su.nb * (unsigned)sizeof(XBin<T>));
+                const __amdgpu_buffer_rsrc_t mr = buffer_range(su.m, su.nb * (unsigned)sizeof(MBin<T>));
+                XBin<T> xb[2];
+                MBin<T> mb[2];
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const unsigned j = (unsigned)(t + TT * k);
+                    xb[k] = load_record<XBin<T>>(xr, j);
+                    mb[k] = load_record<MBin<T>>(mr, j);
+                }
+                env_bins<T, N>(mb, xb, su.k_lo, t, at, ap);
+            }
+            qb_pin(q);
+            C2<T> x[8];
+            T pt[8], pp[8];
+            qb_transform<T, N>(at[0], at[1], x, la, q, t);
+#pragma unroll
+            for (int r = 0; r < 8; ++r) pt[r] = fma(x[r].re, x[r].re, x[r].im * x[r].im);
+            lds_sync<WAVE>();  // every wave is done with `la`
+            qb_transform<T, N>(ap[0], ap[1], x, la, q, t);
+#pragma unroll
+            for (int r = 0; r < 8; ++r) pp[r] = fma(x[r].re, x[r].re, x[r].im * x[r].im);
+            env_maxima<T, N>(pt, pp, c_lo, top_key, near_cnt, it, peak + 3 * u, arg + 3 * u,
+                             q.out0, t);
+        }
+        // the maxima with another sample near them, decided by env_redo (a
+        // station passed over has no counts)
+        vmem_wait_all();
+        lds_sync<WAVE>();
+        unsigned todo = 0;  // lane `it`: its station's components
+        if (lane < kEnvRound)
+            for (int c = c_lo; c < 3; ++c) todo |= near_cnt[c][lane] > 1u ? 1u << c : 0u;
+        unsigned long long redo = __ballot(todo != 0u);
+        lds_sync<WAVE>();
+        for (int i = t; i < 3 * kEnvRound; i += TT) (&near_cnt[0][0])[i] = (&top_key[0][0])[i] = 0;
+        if (redo != 0ull) {  // uniform over the workgroup
+            do {
+                const int it = __builtin_ctzll(redo);
+                redo &= redo - 1;
+                const int64_t uu = u_first + (int64_t)it * step;
+                const Su su = locate(uu);
+                env_redo<T, N, 0>(su.x, su.m, su.nb, su.k_lo, peak + 3 * uu, arg + 3 * uu,
+                               (unsigned)__builtin_amdgcn_readlane((int)todo, it), la, tw, red_v, red_i);
+            } while (redo != 0ull);
+            // (again, so that they are not held in registers meanwhile)
+            int tt = t;
+            asm volatile("" : "+v"(tt));
+            qb_load_lanes<T, N>(q, tw, tt);
+            vmem_wait_all();
+        }
+        lds_sync<WAVE>();
     }
 }
 
@@ -2472,6 +2857,15 @@ static int64_t host_freq_node(const GridDev& g, int64_t k, int n, int64_t fs)
     return std::min<int64_t>(q, g.n_freq - 2);
 }
 
+// Whether the band spans at most the frequency nodes an angular slice holds in LDS.
+static bool band_in_slice(const GridDev& g, const EvParams& p, int64_t fs)
+{
+    if (p.nb == 0) return true;
+    const int64_t f_lo = host_freq_node(g, p.k_lo, p.N, fs);
+    const int64_t f_hi = host_freq_node(g, (int64_t)p.k_lo + p.nb - 1, p.N, fs);
+    return f_lo >= 0 && f_hi - f_lo + 2 <= kMaxSliceNodes;
+}
+
 // The single-direction call in one launch (k_event_fused), where it applies:
 // 2048 or 4096 samples, traces and table in the compute precision, a band of
 // at most 2 N/8 bins spanning at most kMaxSliceNodes frequency nodes.
@@ -2484,11 +2878,7 @@ static bool event_fused(const au_table* tb, const au_event* ev, const EvParams& 
     if ((p.N != 2048 && p.N != 4096) || ev->trace_dtype != tcode || tb->dtype != tcode || p.S < 1)
         return false;
     if (p.nb > 2 * (p.N / 8)) return false;
-    if (p.nb > 0) {
-        const int64_t f_lo = host_freq_node(tb->g, p.k_lo, p.N, ev->fs_hz);
-        const int64_t f_hi = host_freq_node(tb->g, (int64_t)p.k_lo + p.nb - 1, p.N, ev->fs_hz);
-        if (f_lo < 0 || f_hi - f_lo + 2 > kMaxSliceNodes) return false;
-    }
+    if (!band_in_slice(tb->g, p, ev->fs_hz)) return false;
     const C2<T>* tw = twiddles<T>(tb->device);
     if (tw == nullptr) {
         *rc = fail(AU_EDEVICE, "twiddle tables missing on this device");
@@ -3597,13 +3987,56 @@ static int env_spw(int S, int64_t n_dir)
     return spw;
 }
 
+// Workgroups of k_env_peaks the device holds at once, a multiple of 8 (cached;
+// 512 if unknown).
 template <typename T, int N>
-static hipError_t launch_env_n(hipStream_t st, const EvDesc& ev0, int spw, int n_units, const XBin<T>* X,
+static int env_peaks_blocks()
+{
+    static const int blocks = [] {
+        int dev = 0, cus = 0, occ = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_env_peaks<T, N>, N / 8, 0) != hipSuccess ||
+            cus * occ < 8)
+            return 512;
+        return cus * occ / 8 * 8;
+    }();
+    return blocks;
+}
+
+// Whether the envelope peaks of n-sample traces whose largest band is nb bins
+// come from k_env_peaks: it takes a wavefront per 512 samples and bands of at
+// most a quarter of the samples (30-80 MHz at 200 MHz sampling is that).  In
+// float, whose peaks differ from k_unfold_env's in the last digits, not for
+// the direction fit (scores: sums of their squares in double, which a change of
+// kernel would move beyond double's digits) nor, so that fit and scan agree
+// where they are held to each other that closely, for 1024-sample scans.
+static bool env_peaks_applies(bool f32, int n, int nb, bool scores)
+{
+    if (n < 512 || nb > n / 4) return false;
+    return !(f32 && (scores || n == 1024));
+}
+
+// Envelope peaks of n_su station-unfolds: one event's (sunits null; ev0.S
+// stations of every direction, units = workgroups of spw stations) or many
+// events' (evs, sunits and units with one direction each).  k_env_peaks where
+// it applies and no traces are asked for; else k_unfold_env.
+template <typename T, int N>
+static hipError_t launch_env_n(hipStream_t st, const EvDesc& ev0, int spw, int n_units, int64_t n_su, const XBin<T>* X,
                                const MBin<T>* M, T* efield, T* peak, int* arg, const C2<T>* tw,
                                const int* skip = nullptr, const EvDesc* evs = nullptr,
-                               const int4* units = nullptr, int skip_stride = 0, bool total_only = false)
+                               const int2* sunits = nullptr, const int4* units = nullptr, int skip_stride = 0,
+                               bool total_only = false, bool scores = false)
 {
-    constexpr int E = N >= 1024 ? 8 : (N < 16 ? N : 16);
+    if constexpr (N >= 512) {
+        if (efield == nullptr && env_peaks_applies(sizeof(T) == 4, N, ev0.nb, scores)) {
+            const int64_t grid = std::min<int64_t>((n_su + 7) / 8 * 8, env_peaks_blocks<T, N>());
+            hipLaunchKernelGGL((k_env_peaks<T, N>), dim3((unsigned)grid), dim3(N / 8), 0, st, ev0, n_su, X, M, peak,
+                               arg, tw, skip, evs, sunits, skip_stride, total_only ? 1 : 0);
+            return hipGetLastError();
+        }
+    }
+    constexpr int E = env_e<N>();
     constexpr int TT = N / E;
     constexpr int G = groups_per_block<T, N, E, env_bufs<T, E>()>();
     constexpr size_t LDS = ((size_t)G * env_bufs<T, E>() * lds_elems<N>() + env_ltw<T, N, E>()) * sizeof(C2<T>);
@@ -3652,7 +4085,8 @@ static au_status run_envelope(const au_table* tb, const au_event* ev, const EvPa
     switch (p.N) {
 #define X_(NN)                                                                                              \
     case NN:                                                                                                \
-        e = launch_env_n<T, NN>(st, ev0, spw, (int)n_units, X, M, (T*)d_efield, (T*)d_peak, (int*)d_arg, tw); \
+        e = launch_env_n<T, NN>(st, ev0, spw, (int)n_units, (int64_t)n_dir * p.S, X, M, (T*)d_efield,          \
+                                (T*)d_peak, (int*)d_arg, tw);                                                  \
         break;
         AU_FOR_EACH_N(X_)
 #undef X_
@@ -3734,7 +4168,7 @@ __device__ void block_argmax(double& v, int& i)
         for (int w = 1; w < kBlock / 64; ++w) amax_merge(v, i, sv[w], si[w]);
 }
 
-// block-wide sums of K doubles over kBlock threads, result in every thread
+// sums of K doubles over the first kBlock threads of the block, result in every thread
 template <int K>
 __device__ void block_sum(double (&v)[K])
 {
@@ -3742,7 +4176,7 @@ __device__ void block_sum(double (&v)[K])
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         for (int off = 32; off >= 1; off >>= 1) v[k] += __shfl_xor(v[k], off);
-        if ((threadIdx.x & 63) == 0) sv[k][threadIdx.x >> 6] = v[k];
+        if ((threadIdx.x & 63) == 0 && threadIdx.x < kBlock) sv[k][threadIdx.x >> 6] = v[k];
     }
     __syncthreads();
 #pragma unroll
@@ -3778,6 +4212,44 @@ __global__ __launch_bounds__(kBlock) void k_volt_timing(const Tin* __restrict__ 
     }
     block_argmax(bv, bi);
     if (threadIdx.x == 0) t0[blockIdx.x] = bi;
+}
+
+// Least-squares plane wave t = t0 + p x + q y over S stations (times row[s] dt_ns)
+// about the centroid, and the direction of arrival n = (-c p, -c q) on the
+// ground, in degrees; false where the geometry does not determine it.  Summed by
+// the block's first kBlock threads (at least that many); every thread of the
+// block calls it and gets the result.
+__device__ __forceinline__ bool plane_direction(int S, double dt_ns, const double* __restrict__ pos, const int* row,
+                                                double& zen, double& az)
+{
+    const int s0 = threadIdx.x < kBlock ? (int)threadIdx.x : S;
+    double m[3] = {0.0, 0.0, 0.0};
+    for (int s = s0; s < S; s += kBlock) {
+        m[0] += pos[2 * s];
+        m[1] += pos[2 * s + 1];
+        m[2] += (double)row[s] * dt_ns;
+    }
+    block_sum(m);
+    const double inv_s = 1.0 / (double)S;
+    const double mx = m[0] * inv_s, my = m[1] * inv_s, mt = m[2] * inv_s;
+    double c[5] = {0.0, 0.0, 0.0, 0.0, 0.0};  // xx, xy, yy, xt, yt about the centroid
+    for (int s = s0; s < S; s += kBlock) {
+        const double dx = pos[2 * s] - mx, dy = pos[2 * s + 1] - my, dt = (double)row[s] * dt_ns - mt;
+        c[0] += dx * dx;
+        c[1] += dx * dy;
+        c[2] += dy * dy;
+        c[3] += dx * dt;
+        c[4] += dy * dt;
+    }
+    block_sum(c);
+    const double det = c[0] * c[2] - c[1] * c[1];
+    const double p = (c[2] * c[3] - c[1] * c[4]) / det, q = (c[0] * c[4] - c[1] * c[3]) / det;
+    const double nx = -kCMPerNs * p, ny = -kCMPerNs * q;
+    const double sn = fmin(1.0, sqrt(nx * nx + ny * ny));
+    az = atan2(ny, nx) * (180.0 / M_PI);
+    if (az < 0.0) az += 360.0;
+    zen = asin(sn) * (180.0 / M_PI);
+    return det > 1e-12 * c[0] * c[2] && isfinite(zen) && isfinite(az);
 }
 
 // One step of the loop, one block.  state: [0] stop, [1] directions produced,
@@ -3831,34 +4303,10 @@ __device__ __forceinline__ void recon_step_block(int e, int it, int last, int S,
             return;
         }
     }
-    double m[3] = {0.0, 0.0, 0.0};
-    for (int s = threadIdx.x; s < S; s += kBlock) {
-        m[0] += pos[2 * s];
-        m[1] += pos[2 * s + 1];
-        m[2] += (double)row[s] * dt_ns;
-    }
-    block_sum(m);
-    const double inv_s = 1.0 / (double)S;
-    const double mx = m[0] * inv_s, my = m[1] * inv_s, mt = m[2] * inv_s;
-    double c[5] = {0.0, 0.0, 0.0, 0.0, 0.0};  // xx, xy, yy, xt, yt about the centroid
-    for (int s = threadIdx.x; s < S; s += kBlock) {
-        const double dx = pos[2 * s] - mx, dy = pos[2 * s + 1] - my, dt = (double)row[s] * dt_ns - mt;
-        c[0] += dx * dx;
-        c[1] += dx * dy;
-        c[2] += dy * dy;
-        c[3] += dx * dt;
-        c[4] += dy * dt;
-    }
-    block_sum(c);
+    double zen, az;
+    const bool ok = plane_direction(S, dt_ns, pos, row, zen, az);
     if (threadIdx.x != 0) return;
-    const double det = c[0] * c[2] - c[1] * c[1];
-    const double p = (c[2] * c[3] - c[1] * c[4]) / det, q = (c[0] * c[4] - c[1] * c[3]) / det;
-    const double nx = -kCMPerNs * p, ny = -kCMPerNs * q;
-    const double sn = fmin(1.0, sqrt(nx * nx + ny * ny));
-    double az = atan2(ny, nx) * (180.0 / M_PI);
-    if (az < 0.0) az += 360.0;
-    const double zen = asin(sn) * (180.0 / M_PI);
-    if (!(det > 1e-12 * c[0] * c[2]) || !isfinite(zen) || !isfinite(az)) {
+    if (!ok) {
         cur[0] = 0.0;
         cur[1] = 0.0;
         state[3] = 1;
@@ -3903,6 +4351,168 @@ __global__ __launch_bounds__(kBlock) void k_recon_step_coef(int it, int S, doubl
                              nullptr, 0.0, state, 0);
 }
 
+// ---------------------------------------------------------------------------
+// One pass of one event's loop in one launch, a workgroup per station
+// ---------------------------------------------------------------------------
+
+// Traces from an analytic signal a (qb_transform's x, bins shifted down by k_lo):
+// e[n] = Re or, with IM, Im of a[n] exp(2 pi i k_lo n / N), stored in sample order
+// through the exchange buffer.  Every thread must have passed a barrier after
+// its last use of `la`, and passes one before the next.
+template <typename T, int N, bool IM>
+__device__ __forceinline__ void env_store_trace(const C2<T> (&x)[8], int out0, unsigned k_lo,
+                                                const C2<T>* __restrict__ tw, C2<T>* __restrict__ la,
+                                                T* __restrict__ out, int t)
+{
+    constexpr int TT = N / 8;
+    static_assert((N + N / 64) * sizeof(T) <= qb_elems<N>() * sizeof(C2<T>), "one slot per 64 samples between");
+    T* __restrict__ buf = reinterpret_cast<T*>(la);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+        const int n = out0 + TT * r;
+        const C2<T> w = tw[(k_lo * (unsigned)n & (N - 1)) * (kTwN / N)];  // conjugate of the factor
+        buf[n + (n >> 6)] = IM ? fma(x[r].im, w.re, -x[r].re * w.im) : fma(x[r].re, w.re, x[r].im * w.im);
+    }
+    lds_barrier();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int n = t + TT * i;
+        __builtin_nontemporal_store(buf[n + (n >> 6)], out + n);
+    }
+}
+
+// Pass `it` (times hist row `it` -> direction `it` -> times row it + 1) of the
+// loop of an event of up to a few stations per CU, bound by latency: a chain of
+// launches that each work for a few microseconds.  Every workgroup repeats the
+// step (the convergence test of rows it - 1 and it, the plane fit, the
+// direction's angular slice in LDS) and takes the coefficients of its own two
+// bins per thread from it, as k_event_fused does, then the envelope maxima of
+// its station as k_env_peaks, so that a pass is one launch with nothing between
+// it and the next.  Workgroup 0 writes the direction and the state (as
+// recon_step_block: [0] stop, [1] directions, [2] converged, [3] degenerate).
+// The coefficient row in M is written only for env_redo (by every workgroup that
+// needs it, the same values).  Needs a plane fit's kBlock threads (N >= 2048)
+// and at most kMaxSliceNodes frequency nodes in the band.
+// 124 stations x 4096 samples in double, traces kept, two passes: 90 -> 75 us per
+// call against three steps with coefficients (11 us each) and two envelope
+// launches (13 us); 21 us a pass.
+template <typename Tt, typename T, int N>
+__global__ __launch_bounds__(N / 8) void k_recon_pass(int it, EvDesc ev, double dt_ns, const double* __restrict__ pos,
+                                                       int* hist, double* dirs, int* state,
+                                                       const C2<Tt>* __restrict__ nodes, GridDev gd, int64_t fs,
+                                                       double fallback_rel, double singular_rel,
+                                                       const XBin<T>* __restrict__ X, MBin<T>* M,
+                                                       T* __restrict__ efield, T* __restrict__ peak,
+                                                       int* __restrict__ arg, const C2<T>* __restrict__ tw)
+{
+    constexpr int TT = N / 8, NW = N / 512;
+    static_assert(TT >= kBlock, "the plane fit's threads");
+    __shared__ C2<T> la[qb_elems<N>()];
+    __shared__ C2<T> sl[kMaxSliceNodes][4];
+    __shared__ T red_v[3][NW];
+    __shared__ int red_i[3][NW];
+    __shared__ unsigned top_key[3][1], near_cnt[3][1];
+    const int t = threadIdx.x, s = blockIdx.x, S = ev.S;
+    const unsigned nb = (unsigned)ev.nb, k_lo = (unsigned)ev.k_lo;
+    if (it > 0 && state[0]) return;
+    // what the direction does not decide comes first
+    QbTwiddles<T, N> q;
+    qb_load_uniform<T, N>(q, tw, t);
+    qb_load_lanes<T, N>(q, tw, t);
+    const XBin<T>* __restrict__ Xs = X + (int64_t)s * nb;
+    const __amdgpu_buffer_rsrc_t xr = buffer_range(Xs, nb * (unsigned)sizeof(XBin<T>));
+    XBin<T> xb[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) xb[k] = load_record<XBin<T>>(xr, (unsigned)(t + TT * k));
+    if (t < 3) top_key[t][0] = near_cnt[t][0] = 0;
+    const int* row = hist + (int64_t)it * S;
+    if (it > 0) {
+        int changed = 0;
+        for (int k = t; k < S; k += TT) changed |= row[k] != row[k - S];
+        if (!__syncthreads_or(changed)) {
+            if (s == 0 && t == 0) {
+                state[0] = 1;
+                state[2] = 1;
+            }
+            return;
+        }
+    }
+    double zen, az;
+    const bool ok = plane_direction(S, dt_ns, pos, row, zen, az);
+    if (s == 0 && t == 0) {
+        if (it == 0) state[2] = 0;
+        state[0] = state[3] = ok ? 0 : 1;
+        state[1] = it + (ok ? 1 : 0);
+        if (ok) {
+            dirs[2 * it] = zen;
+            dirs[2 * it + 1] = az;
+        }
+    }
+    if (!ok) return;  // uniform
+    int iz, ia, ja;
+    double tz, ta;
+    angle_cells(gd, zen, az, iz, tz, ia, ja, ta);
+    int f_lo = 0, n_nodes = 0;
+    if (nb > 0) {
+        int f_hi;
+        double tdummy;
+        freq_cell(gd, (int64_t)k_lo, N, fs, f_lo, tdummy);
+        freq_cell(gd, (int64_t)(k_lo + nb - 1), N, fs, f_hi, tdummy);
+        n_nodes = f_hi - f_lo + 2;
+    }
+    for (int i = t; i < 4 * n_nodes; i += TT)
+        sl[i >> 2][i & 3] = slice1<Tt, T>(nodes, gd, f_lo + (i >> 2), i & 3, iz, (T)tz, ia, ja, (T)ta);
+    __syncthreads();
+    const T inv_n = (T)(1.0 / (double)N);
+    MBin<T> mb[2];
+    unsigned n_fb = 0, n_sg = 0;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const unsigned j = (unsigned)(t + TT * k);
+        mb[k] = MBin<T>{};
+        if (j < nb) {
+            int ifr;
+            double tf;
+            freq_cell(gd, (int64_t)(k_lo + j), N, fs, ifr, tf);
+            const int li = ifr - f_lo;
+            C2<T> h[4];
+#pragma unroll
+            for (int cp = 0; cp < 4; ++cp) h[cp] = clerp(sl[li][cp], sl[li + 1][cp], (T)tf);
+            mb[k] = coef_from_h<T>(h, N, inv_n, fallback_rel, singular_rel, n_fb, n_sg);
+        }
+    }
+    C2<T> at[2], ap[2];
+    env_bins<T, N>(mb, xb, k_lo, t, at, ap);
+    C2<T> x[8];
+    T pt[8], pp[8];
+    T* out = efield != nullptr ? efield + (int64_t)s * 2 * N : nullptr;
+    qb_transform<T, N>(at[0], at[1], x, la, q, t);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) pt[r] = fma(x[r].re, x[r].re, x[r].im * x[r].im);
+    lds_barrier();
+    if (out != nullptr) {
+        env_store_trace<T, N, false>(x, q.out0, k_lo, tw, la, out, t);
+        lds_barrier();
+    }
+    qb_transform<T, N>(ap[0], ap[1], x, la, q, t);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) pp[r] = fma(x[r].re, x[r].re, x[r].im * x[r].im);
+    env_maxima<T, N>(pt, pp, 0, top_key, near_cnt, 0, peak + 3 * s, arg + 3 * s, q.out0, t);
+    if (out != nullptr) env_store_trace<T, N, true>(x, q.out0, k_lo, tw, la, out + N, t);
+    __syncthreads();  // the counts, and every store of this workgroup
+    unsigned redo = 0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) redo |= near_cnt[c][0] > 1u ? 1u << c : 0u;
+    if (redo != 0u) {  // uniform
+        for (int k = 0; k < 2; ++k)
+            if ((unsigned)(t + TT * k) < nb) M[t + TT * k] = mb[k];
+        __syncthreads();
+        env_redo<T, N, 1>(Xs, M, nb, k_lo, peak + 3 * s, arg + 3 * s, redo, la, tw, red_v, red_i);
+        __syncthreads();
+    }
+    if (t == 0) hist[(int64_t)(it + 1) * S + s] = arg[3 * s + 2];
+}
+
 namespace {
 
 struct ReconLayout {
@@ -3934,6 +4544,17 @@ au_status check_recon(const au_table* tb, const au_event* ev, int32_t max_iter, 
 }
 
 }  // namespace
+
+// Whether the loop of one event runs as one launch per pass (k_recon_pass): 2048
+// or 4096 samples (the plane fit's threads), a band of at most a quarter of
+// them (k_env_peaks's transform) within the frequency nodes LDS holds, and at
+// most four stations per CU of the smallest part, beyond which the step that
+// every workgroup repeats (about 6 us) costs more than the launches it saves.
+static bool recon_pass_applies(const au_table* tb, const au_event* ev, const EvParams& p)
+{
+    if ((p.N != 2048 && p.N != 4096) || p.nb > p.N / 4 || p.S > 1024) return false;
+    return band_in_slice(tb->g, p, ev->fs_hz);
+}
 
 // A pinned host buffer of the calling thread of at least `bytes` (null if it
 // cannot be allocated: callers then copy to pageable memory).  One per
@@ -4037,7 +4658,8 @@ static au_status run_reconstruct(const au_table* tb, const au_event* ev, const E
             switch (p.N) {
 #define X_(NN)                                                                                               \
     case NN:                                                                                                 \
-        e = launch_env_n<T, NN>(st, ev0, spw, chunks, X, M, (T*)d_efield, peak, arg, tw, (const int*)state); \
+        e = launch_env_n<T, NN>(st, ev0, spw, chunks, p.S, X, M, (T*)d_efield, peak, arg, tw,                \
+                                (const int*)state);                                                          \
         break;
                 AU_FOR_EACH_N(X_)
 #undef X_
@@ -4067,6 +4689,37 @@ static au_status run_reconstruct(const au_table* tb, const au_event* ev, const E
         HIP_TRY(hipStreamSynchronize(st));
         return AU_OK;
     };
+    if (recon_pass_applies(tb, ev, p)) {
+        // one launch per pass, results read after two (the usual number) and
+        // then every four; the last pass enqueued has no successor that tests
+        // its times, so they are compared here
+        int it = 0;
+        for (int upto = std::min(2, max_iter);; upto = std::min(upto + 4, max_iter)) {
+            for (; it < upto; ++it) {
+#define PASS_(TT, NN)                                                                                                \
+    hipLaunchKernelGGL((k_recon_pass<TT, T, NN>), dim3(p.S), dim3(NN / 8), 0, st, it, ev0, dt_ns, (const double*)pos, \
+                       hist, dirs, state, (const C2<TT>*)tb->d_nodes, tb->g, ev->fs_hz, ev->fallback_rel,            \
+                       ev->singular_rel, X, M, (T*)d_efield, peak, arg, tw)
+                if (tb->dtype == AU_F64 && p.N == 2048)
+                    PASS_(double, 2048);
+                else if (tb->dtype == AU_F64)
+                    PASS_(double, 4096);
+                else if (p.N == 2048)
+                    PASS_(float, 2048);
+                else
+                    PASS_(float, 4096);
+#undef PASS_
+                e = hipGetLastError();
+                if (e != hipSuccess)
+                    return fail(AU_EDEVICE, std::string("reconstruction pass: ") + hipGetErrorString(e));
+            }
+            const au_status s = fetch();
+            if (s != AU_OK || h_state[0] != 0) return s;
+            const int32_t* last = h_times + (size_t)it * p.S;
+            h_state[2] = std::equal(last, last + p.S, last - p.S) ? 1 : 0;
+            if (h_state[2] != 0 || it == max_iter) return AU_OK;
+        }
+    }
     int op = 0;
     for (int check = std::min(4, n_ops - 1);; check = std::min(check + 8, n_ops - 1)) {
         for (; op <= check; ++op) {
@@ -4307,8 +4960,8 @@ static au_status run_fit(const au_table* tb, const au_event* ev, const EvParams&
         switch (p.N) {
 #define X_(NN)                                                                                       \
     case NN:                                                                                         \
-        e = launch_env_n<T, NN>(st, ev0, spw, nc * chunks, X, M, (T*)nullptr, peak, arg, tw, nullptr,   \
-                                nullptr, nullptr, 0, true);                                          \
+        e = launch_env_n<T, NN>(st, ev0, spw, nc * chunks, (int64_t)nc * p.S, X, M, (T*)nullptr, peak, arg, tw, \
+                                nullptr, nullptr, nullptr, nullptr, 0, true, true);                  \
         break;
             AU_FOR_EACH_N(X_)
 #undef X_
@@ -4537,8 +5190,9 @@ static au_status run_reconstruct_batch(const au_table* tb, const au_event* ev, c
         switch (p.N) {
 #define X_(NN)                                                                                          \
     case NN:                                                                                            \
-        e = launch_env_n<T, NN>(st, ev0, spw, (int)n_eunits, X, M, (T*)nullptr, peak, arg, tw,          \
-                                (const int*)state, (const EvDesc*)evs, (const int4*)eunits, 4, true);   \
+        e = launch_env_n<T, NN>(st, ev0, spw, (int)n_eunits, stot, X, M, (T*)nullptr, peak, arg, tw,    \
+                                (const int*)state, (const EvDesc*)evs, (const int2*)sunits,             \
+                                (const int4*)eunits, 4, true);                                          \
         break;
             AU_FOR_EACH_N(X_)
 #undef X_

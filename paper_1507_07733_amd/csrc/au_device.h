@@ -350,12 +350,14 @@ constexpr int lds_zero_slot() { return N + 1; }
 //             wavefront (fft4096_xw): one through the wavefront's own LDS
 //             slots with no workgroup barrier, one as a register transpose;
 //             one workgroup exchange per transform instead of three.
-enum { TW_TABLE = 0, TW_REG = 1, TW_SPLIT = 2, TW_HYB = 3, TW_LF = 4, TW_LFR = 5, TW_LFW = 6 };
+//   TW_LFT:   the TW_LF pairs read from the table each time (fft only; the
+//             envelope kernel's rare path, which has no registers set aside).
+enum { TW_TABLE = 0, TW_REG = 1, TW_SPLIT = 2, TW_HYB = 3, TW_LF = 4, TW_LFR = 5, TW_LFW = 6, TW_LFT = 7 };
 
 // Twiddles of the early passes in a per-workgroup LDS table.
 constexpr bool tw_lds_early(int mode) { return mode == TW_HYB || mode == TW_LF; }
 // Fused multiply-add butterflies with (tangent, cosine) twiddle pairs.
-constexpr bool tw_lf(int mode) { return mode == TW_LF || mode == TW_LFR || mode == TW_LFW; }
+constexpr bool tw_lf(int mode) { return mode == TW_LF || mode == TW_LFR || mode == TW_LFW || mode == TW_LFT; }
 // Every pass's twiddles in registers.
 constexpr bool tw_all_reg(int mode) { return mode == TW_REG || mode == TW_LFR || mode == TW_LFW; }
 // (tangent, cosine) pairs per butterfly of a radix-R pass in TW_LF, TW_LFR, TW_LFW.
@@ -606,7 +608,9 @@ __device__ __forceinline__ void fft_pass(C2<T> (&x)[E], C2<T>* __restrict__ lds,
             C2<T> L[LE];
 #pragma unroll
             for (int e = 0; e < LE; ++e) {
-                if constexpr (TWMODE == TW_LF && NS < TT)
+                if constexpr (TWMODE == TW_LFT)
+                    L[e] = lf_tab<SIGN>(tw, k * (kTwN / (NS * R)), e);
+                else if constexpr (TWMODE == TW_LF && NS < TT)
                     L[e] = lf_sign<SIGN>(ltw[ltw_offset<N, E, RMAX, TW_LF>(NS) + e * NS + k]);
                 else
                     L[e] = lf_sign<SIGN>(w[OFF + m * LE + e]);
@@ -1064,6 +1068,158 @@ __device__ __forceinline__ void fft4096_xw2(C2<T> (&x)[8], C2<T> (&y)[8], C2<T>*
     for (int r = 0; r < 8; ++r) y[r] = lb[xw_slot(512 * r + 64 * wv + l)];
     xw_pass<T, 512, SIGN, TWMODE>(x, w, ltw, t);
     xw_pass<T, 512, SIGN, TWMODE>(y, w, ltw, t);
+}
+
+// ---------------------------------------------------------------------------
+// Quarter-band inverse transform (k_env_peaks): a[n] = sum_j A[j] exp(2 pi i j n / N),
+// n < N, of a sequence whose elements past N/4 are zero, N = 512 R2 with R2 in
+// {1, 2, 4, 8}, on R2 wavefronts of 64 threads with 8 values each.  Thread
+// t = 64 w + l, lane l = 8 lh + ll, takes A[t] and A[t + N/8] (its elements
+// e = (N/8) e3 + t, e3 < 2) from registers: in digits e = (N/8) e3 + 64 e2 +
+// 8 e1 + e0 with e2 = w, e1 = lh, e0 = ll, the passes combine e3 (radix 8, six
+// of its inputs zero, no twiddles), e2 (radix R2), e1 and e0 (radix 8).  The
+// register index holds the digit a pass combines; between passes it changes
+// places with the wave (through LDS, the transform's only workgroup barrier;
+// none at N = 512), with lane bits 3-5 (register transpose) and with lane
+// bits 0-2 (the wavefront's own LDS block).  Each pass's twiddle is
+// exp(2 pi i e K / (length so far)), K the output digits found so far: for the
+// second pass uniform over the wavefront (scalar registers).  Results stay
+// where the last pass leaves them: x[r] = a[out0 + (N/8) r].
+// ---------------------------------------------------------------------------
+
+// Slots of a wavefront's block of the exchange buffer: 8 rows of 64 for the
+// workgroup exchange; for the transpose with lane bits 0-2, element (lh, ll,
+// register b) at 65 ll + 8 lh + b, so that both sides address a lane base plus a
+// constant and neither has bank conflicts (8- and 16-byte elements).  The
+// transpose with lane bits 3-5 through LDS as well costs a ninth of the VALU
+// instructions less in float but measured the same (665 against 661 us below),
+// and 4 % more in double (LDS bandwidth).
+constexpr int kQbBlock = 520;
+template <int N>
+constexpr int qb_waves() { return N / 512; }
+template <int N>
+constexpr int qb_elems() { return qb_waves<N>() * kQbBlock; }
+
+template <typename T, int N>
+struct QbTwiddles {
+    C2<T> l2[4];  // second pass: 8 / R2 butterflies of lf_entries(R2) pairs
+    C2<T> l3[4], l4[4];
+    int out0;     // sample of x[0]
+};
+
+// A value that is the same in every lane, in scalar registers.
+template <typename V>
+__device__ __forceinline__ V uniform_value(const V& v)
+{
+    struct Words {
+        int w[sizeof(V) / 4];
+    };
+    Words d = __builtin_bit_cast(Words, v);
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(V) / 4); ++i) d.w[i] = __builtin_amdgcn_readfirstlane(d.w[i]);
+    return __builtin_bit_cast(V, d);
+}
+
+// The second pass's twiddles (uniform over the wavefront), and the rest.
+template <typename T, int N>
+__device__ __forceinline__ void qb_load_uniform(QbTwiddles<T, N>& q, const C2<T>* __restrict__ tw, int t)
+{
+    constexpr int R2 = qb_waves<N>();
+    if constexpr (R2 > 1) {
+        constexpr int LE = lf_entries(R2);
+        const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+#pragma unroll
+        for (int b = 0; b < 8 / R2; ++b)
+#pragma unroll
+            for (int e = 0; e < LE; ++e)
+                q.l2[b * LE + e] = uniform_value(lf_tab<+1>(tw, (w + R2 * b) * (512 / R2), e));
+    }
+}
+template <typename T, int N>
+__device__ __forceinline__ void qb_load_lanes(QbTwiddles<T, N>& q, const C2<T>* __restrict__ tw, int t)
+{
+    constexpr int R2 = qb_waves<N>();
+    const int w = R2 == 1 ? 0 : t >> 6, lh = (t >> 3) & 7, ll = t & 7;
+    const int k3 = w + R2 * (lh / R2) + 8 * (lh % R2);
+    const int k4 = k3 + 8 * R2 * ll;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        q.l3[e] = lf_tab<+1>(tw, k3 * (64 / R2), e);
+        q.l4[e] = lf_tab<+1>(tw, k4 * (8 / R2), e);
+    }
+    q.out0 = k4;
+}
+
+// States the lanes' twiddles as new values (no instruction).  At the top of a
+// loop over transforms this keeps their negations, which the butterflies take as
+// source modifiers, from being computed ahead of the loop into registers of their
+// own.
+template <typename T, int N>
+__device__ __forceinline__ void qb_pin(QbTwiddles<T, N>& q)
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        asm volatile("" : "+v"(q.l3[e].re), "+v"(q.l3[e].im));
+        asm volatile("" : "+v"(q.l4[e].re), "+v"(q.l4[e].im));
+    }
+}
+
+// The first pass: v[q] = a0 + a1 exp(2 pi i q / 8).
+template <typename T>
+__device__ __forceinline__ void qb_first(const C2<T> a0, const C2<T> a1, C2<T> (&v)[8])
+{
+    constexpr T c = (T)kQuadCos32[4];  // cos(pi / 4)
+    const C2<T> d{a1.re - a1.im, a1.re + a1.im};
+    v[0] = cadd(a0, a1);
+    v[4] = csub(a0, a1);
+    v[2] = C2<T>{a0.re - a1.im, a0.im + a1.re};
+    v[6] = C2<T>{a0.re + a1.im, a0.im - a1.re};
+    v[1] = C2<T>{fma(c, d.re, a0.re), fma(c, d.im, a0.im)};
+    v[5] = C2<T>{fma(-c, d.re, a0.re), fma(-c, d.im, a0.im)};
+    v[3] = C2<T>{fma(-c, d.im, a0.re), fma(c, d.re, a0.im)};
+    v[7] = C2<T>{fma(c, d.im, a0.re), fma(-c, d.re, a0.im)};
+}
+
+// `la` holds qb_elems<N>() slots; every thread of the workgroup must have
+// passed a barrier after its last use of `la` by an earlier call (not at N =
+// 512, where a wavefront has its own).
+template <typename T, int N>
+__device__ __forceinline__ void qb_transform(const C2<T> a0, const C2<T> a1, C2<T> (&x)[8], C2<T>* __restrict__ la,
+                                             const QbTwiddles<T, N>& q, int t)
+{
+    constexpr int R2 = qb_waves<N>();
+    const int w = t >> 6, l = t & 63;
+    C2<T>* __restrict__ blk = la + kQbBlock * w;
+    qb_first(a0, a1, x);
+    if constexpr (R2 > 1) {
+        // output digit n0 = r goes to wave n0 mod R2, in its rows (n0 / R2) R2 + e2
+        C2<T>* __restrict__ put = la + 64 * w + l;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) put[kQbBlock * (r % R2) + 64 * ((r / R2) * R2)] = x[r];
+        lds_barrier();
+#pragma unroll
+        for (int r = 0; r < 8; ++r) x[r] = blk[64 * r + l];
+        constexpr int LE = lf_entries(R2);
+#pragma unroll
+        for (int b = 0; b < 8 / R2; ++b) lf_dft<R2, +1>(x + b * R2, q.l2 + b * LE);
+    }
+    // (the passes are kept apart: interleaved, they need more registers than
+    // three workgroups per CU leave in float, and spill)
+    __builtin_amdgcn_sched_barrier(0);
+    xw_transpose_hi(x);
+    __builtin_amdgcn_sched_barrier(0);
+    lf_dft<8, +1>(x, q.l3);
+    __builtin_amdgcn_sched_barrier(0);
+    {
+        C2<T>* __restrict__ put = blk + 65 * (l & 7) + (l & 0x38);
+#pragma unroll
+        for (int b = 0; b < 8; ++b) put[b] = x[b];
+        lds_sync<true>();
+#pragma unroll
+        for (int a = 0; a < 8; ++a) x[a] = blk[65 * a + l];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    lf_dft<8, +1>(x, q.l4);
 }
 
 // Maximum of unsigned keys over the wavefront, uniform.  (DPP row shifts by 1,
