@@ -147,7 +147,7 @@ au_status au_band_bins(const au_event* ev, int32_t* k_lo, int32_t* n_band);
  *   d_efield: [S][2][N] output (E_theta, E_phi), float or double per ev->prec.
  *   d_work:   workspace of au_workspace_bytes(ev, 1) bytes, or NULL to let the
  *             library take it from the stream-ordered pool (hipMallocAsync).
- * Events of 2048 or 4096 samples whose traces and table are in the compute
+ * Events of 256 samples or more whose traces and table are in the compute
  * precision and whose band holds at most N/4 bins run in one launch (one
  * workgroup per station: forward transform, the direction's coefficients,
  * solve, inverse transform) and leave d_work untouched (a given workspace
@@ -208,7 +208,9 @@ au_status au_unfold_direction_scan_noalloc(const au_table* table, const au_event
  *   d_arg  [n_dir][S][3] int32: the smallest n attaining it.
  * d_efield ([n_dir][S][2][N], nullable) also receives the traces.  The
  * Hilbert transform uses -i sgn(k) (sgn 0 at DC and Nyquist); the opposite
- * sign gives the same envelope.  Workspace as au_unfold_direction_scan.
+ * sign gives the same envelope.  The samples do not depend on whether traces
+ * are asked for; the maxima do in their last digits (without traces they come
+ * from the analytic signal's transform).  Workspace as au_unfold_direction_scan.
  */
 au_status au_unfold_envelope_scan(const au_table* table, const au_event* ev, const void* d_volt,
                                   int32_t n_dir, const double* h_dirs, void* d_efield, void* d_peak,

@@ -60,7 +60,7 @@ extern "C" const char* au_version(void) { return "aeraunfold 0.1 gfx950"; }
 
 // Zenith cell and weight; positions outside the grid are clamped to it.
 // Azimuth cell, its periodic neighbour and weight.
-__device__ __forceinline__ void angle_cells(const GridDev& g, double zen, double az, int& iz,
+__host__ __device__ __forceinline__ void angle_cells(const GridDev& g, double zen, double az, int& iz,
                                             double& tz, int& ia, int& ja, double& ta)
 {
     double v = (zen - g.zen0) / g.dzen;
@@ -1325,7 +1325,14 @@ __global__ __launch_bounds__(N / 8) __attribute__((amdgpu_waves_per_eu(4))) void
 // One event, one direction, in one launch (the latency path)
 // ---------------------------------------------------------------------------
 
-// The single-direction call (au_unfold_event) for 2048 and 4096 samples:
+// A direction's cells, worked out on the host (the device's operations): the
+// kernel's first instructions are then its loads.
+struct SliceCells {
+    int iz, ia, ja, f_lo, n_nodes;
+    double tz, ta;
+};
+
+// The single-direction call (au_unfold_event) from 256 samples up:
 // one workgroup per station runs the operations of the three launches of
 // the general path -- the forward transform and in-band split of its two
 // channel traces (as the fused kernel), the direction's coefficients of the
@@ -1335,16 +1342,19 @@ __global__ __launch_bounds__(N / 8) __attribute__((amdgpu_waves_per_eu(4))) void
 // bins), and the staging, inverse transform and stores of k_unfold -- so a
 // small event pays one launch instead of three.  Workgroup 0 counts the
 // fallback and singular bins (once per direction, as k_coef).  Needs bands
-// of at most 2 N/8 bins and at most kMaxSliceNodes frequency nodes.
+// of at most 2 N/8 bins and at most kMaxSliceNodes frequency nodes.  Bound by
+// latency; 57 stations x 1024 samples in float, one launch against three: 16.0
+// -> 9.3 us per call (the host's part; the launch alone 8.5), 124 x 1024 in
+// double 17.1 -> 9.1.  No more than the three launches also where the device is
+// full: 3000 stations x 1024 in double 46.8 -> 46.7 us, x 256 in float 25.4 -> 16.7.
 template <typename Tt, typename T, int N>
 __global__ __launch_bounds__(N / 8) void k_event_fused(const C2<Tt>* __restrict__ nodes, GridDev gd, EvDesc ev,
-                                                       const T* __restrict__ volt, double zen, double az, int64_t fs,
+                                                       const T* __restrict__ volt, SliceCells cells, int64_t fs,
                                                        double fallback_rel, double singular_rel,
                                                        T* __restrict__ efield, const C2<T>* __restrict__ tw,
                                                        unsigned long long* __restrict__ counts)
 {
     constexpr int E = 8, RMAX = 8, TT = N / E, PF = 2;
-    static_assert(TT >= 256, "one transform per workgroup");
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ C2<T> sl[kMaxSliceNodes][4];
     __shared__ unsigned int cnt[2];
@@ -1358,20 +1368,11 @@ __global__ __launch_bounds__(N / 8) void k_event_fused(const C2<Tt>* __restrict_
     if (t == 0) zero_slot_clear<T, N>(smem, 0);
     if (t < 2) cnt[t] = 0;
     // the direction's angular slice at the frequency nodes the band spans
-    int iz, ia, ja;
-    double tz, ta;
-    angle_cells(gd, zen, az, iz, tz, ia, ja, ta);
     const unsigned nb = (unsigned)ev.nb, k_lo = (unsigned)ev.k_lo;
-    int f_lo = 0, n_nodes = 0;
-    if (nb > 0) {
-        int f_hi;
-        double tdummy;
-        freq_cell(gd, (int64_t)k_lo, N, fs, f_lo, tdummy);
-        freq_cell(gd, (int64_t)(k_lo + nb - 1), N, fs, f_hi, tdummy);
-        n_nodes = f_hi - f_lo + 2;
-    }
-    for (int it = t; it < 4 * n_nodes; it += TT)
-        sl[it >> 2][it & 3] = slice1<Tt, T>(nodes, gd, f_lo + (it >> 2), it & 3, iz, (T)tz, ia, ja, (T)ta);
+    const int f_lo = cells.f_lo;
+    for (int it = t; it < 4 * cells.n_nodes; it += TT)
+        sl[it >> 2][it & 3] = slice1<Tt, T>(nodes, gd, f_lo + (it >> 2), it & 3, cells.iz, (T)cells.tz, cells.ia,
+                                            cells.ja, (T)cells.ta);
     // the station's traces: forward transform conj(F+(conj z)), z = V_0 + i V_1
     const T* __restrict__ V = volt + ev.volt_off + (int64_t)s * 2 * N;
     C2<T> x[E];
@@ -1379,7 +1380,12 @@ __global__ __launch_bounds__(N / 8) void k_event_fused(const C2<Tt>* __restrict_
     for (int i = 0; i < E; ++i) x[i] = C2<T>{V[t + TT * i], V[N + t + TT * i]};
     vmem_wait_all();
     lds_barrier();  // twiddle table, zero slot, slice and counters written
-    fft_pp<T, N, E, -1, TW_LF, RMAX, false>(x, lb, la, tw, t, w, ltw);
+    // (three exchanges from 1024 samples up, two below: either way the last
+    // gathers lb, and the split can write la at once)
+    if constexpr (num_passes<N, RMAX>() % 2 == 0)
+        fft_pp<T, N, E, -1, TW_LF, RMAX, false>(x, lb, la, tw, t, w, ltw);
+    else
+        fft_pp<T, N, E, -1, TW_LF, RMAX, false>(x, la, lb, tw, t, w, ltw);
     // in-band split of this thread's bins through la (gathered last before
     // the transform's final exchange): X_0 = (Z[k] + conj Z[N-k]) / 2,
     // X_1 = (Z[k] - conj Z[N-k]) / 2i
@@ -2867,7 +2873,7 @@ static bool band_in_slice(const GridDev& g, const EvParams& p, int64_t fs)
 }
 
 // The single-direction call in one launch (k_event_fused), where it applies:
-// 2048 or 4096 samples, traces and table in the compute precision, a band of
+// from 256 samples up, traces and table in the compute precision, a band of
 // at most 2 N/8 bins spanning at most kMaxSliceNodes frequency nodes.
 // Returns false (nothing enqueued) where it does not apply.
 template <typename T>
@@ -2875,8 +2881,7 @@ static bool event_fused(const au_table* tb, const au_event* ev, const EvParams& 
                         double az, void* d_efield, hipStream_t st, uint64_t* d_counts, au_status* rc)
 {
     constexpr int tcode = sizeof(T) == 8 ? AU_F64 : AU_F32;
-    if ((p.N != 2048 && p.N != 4096) || ev->trace_dtype != tcode || tb->dtype != tcode || p.S < 1)
-        return false;
+    if (p.N < 256 || ev->trace_dtype != tcode || tb->dtype != tcode || p.S < 1) return false;
     if (p.nb > 2 * (p.N / 8)) return false;
     if (!band_in_slice(tb->g, p, ev->fs_hz)) return false;
     const C2<T>* tw = twiddles<T>(tb->device);
@@ -2890,15 +2895,25 @@ static bool event_fused(const au_table* tb, const au_event* ev, const EvParams& 
     ev0.D = 1;
     ev0.k_lo = p.k_lo;
     ev0.nb = p.nb;
+    SliceCells cells{};
+    angle_cells(tb->g, zen, az, cells.iz, cells.tz, cells.ia, cells.ja, cells.ta);
+    if (p.nb > 0) {
+        cells.f_lo = (int)host_freq_node(tb->g, p.k_lo, p.N, ev->fs_hz);
+        cells.n_nodes =
+            (int)host_freq_node(tb->g, (int64_t)p.k_lo + p.nb - 1, p.N, ev->fs_hz) - cells.f_lo + 2;
+    }
 #define EVF_(NN)                                                                                                 \
     hipLaunchKernelGGL((k_event_fused<T, T, NN>), dim3(p.S), dim3(NN / 8),                                       \
                        (2 * lds_elems<NN>() + ltw_count<NN, 8, 8, TW_LF>()) * sizeof(C2<T>), st,                  \
-                       (const C2<T>*)tb->d_nodes, tb->g, ev0, (const T*)d_volt, zen, az, ev->fs_hz,               \
+                       (const C2<T>*)tb->d_nodes, tb->g, ev0, (const T*)d_volt, cells, ev->fs_hz,                 \
                        ev->fallback_rel, ev->singular_rel, (T*)d_efield, tw, (unsigned long long*)d_counts)
-    if (p.N == 2048)
-        EVF_(2048);
-    else
-        EVF_(4096);
+    switch (p.N) {
+        case 256: EVF_(256); break;
+        case 512: EVF_(512); break;
+        case 1024: EVF_(1024); break;
+        case 2048: EVF_(2048); break;
+        default: EVF_(4096); break;
+    }
 #undef EVF_
     const hipError_t e = hipGetLastError();
     *rc = e == hipSuccess ? AU_OK : fail(AU_EDEVICE, std::string("k_event_fused: ") + hipGetErrorString(e));
