@@ -1810,12 +1810,12 @@ __global__ __launch_bounds__((N / E) > kBlock ? (N / E) : kBlock) void k_unfold_
 // operations (env_redo), which decide.  That is a few stations in 10^5 for
 // traces with noise, and every station of a field that is zero.
 
-// Relative distance in amplitude, to the total field's maximum, within which
-// two samples may change places between the two evaluations: 2^-15 (float),
-// 2^-44 (double).  Either transform is off by at most about 2 log2(N) u of the
-// total field's largest magnitude (u = 2^-24 or 2^-53; the error observed is a
-// tenth of that), and four such errors (two samples, two evaluations) can add
-// up: 96 u at N = 4096, taken with a factor of five to spare.
+// Two samples may change places between the two evaluations within kEnvNear of
+// the total field's maximum in amplitude: 2^-17 (float), 2^-46 (double).  Either
+// transform is off by at most about 2 log2(N) u of the total field's largest
+// magnitude (u = 2^-24 or 2^-53; the error observed is a tenth of that), and four
+// such errors (two samples, two evaluations) can add up: 96 u at N = 4096, and
+// kEnvNear is 128 u.
 // Squares below this are decided by env_redo too: they may have lost bits to
 // underflow.
 template <typename T>
@@ -1832,14 +1832,17 @@ __device__ __forceinline__ unsigned env_key(double v) { return (unsigned)__doubl
 // The smallest key that counts as near the key m of a component's largest
 // square, R2 the total's: an amplitude within kEnvNear R of sqrt(m) has a square
 // above m (1 - 2 kEnvNear R / sqrt(m)); a relative step of 2^-b moves a key by
-// at most 2^(B - b) (B one more than its mantissa bits), and R / sqrt(m) is below
-// 2^((e + 2) / 2) for a difference of e in the binary exponents.
+// at most 2^(B - b) (B one more than its mantissa bits), and R / sqrt(m) is 1 for
+// the total itself and below 2^((e + 1) / 2) for a difference of e in the binary
+// exponents.  (Float: 256 keys for the total, which one station in some
+// thousands has another sample in; double, whose keys are coarser than kEnvNear:
+// two, one in 10^5.)
 template <typename T>
-__device__ __forceinline__ unsigned env_near_key(unsigned m, unsigned r2)
+__device__ __forceinline__ unsigned env_near_key(unsigned m, unsigned r2, bool total)
 {
     constexpr int MB = sizeof(T) == 4 ? 23 : 20;
-    constexpr int STEP = sizeof(T) == 4 ? MB + 1 - 15 + 1 : 0;  // log2 of 2 kEnvNear 2^B (at least 1 key)
-    const int h = STEP + (((int)(r2 >> MB) - (int)(m >> MB) + 2) >> 1) - (sizeof(T) == 4 ? 0 : 22);
+    constexpr int STEP = MB + 1 + 1 - (sizeof(T) == 4 ? 17 : 46);  // log2 of 2 kEnvNear 2^B
+    const int h = STEP + (total ? 0 : ((int)(r2 >> MB) - (int)(m >> MB) + 2) >> 1);
     const unsigned d = h <= 0 ? 2u : (h >= 31 ? m : (1u << h) + 1u);
     return d >= m ? 0u : m - d;
 }
@@ -1863,12 +1866,14 @@ __device__ __attribute__((noinline)) void env_redo(const XBin<T>* __restrict__ X
                                          int (*red_i)[N / 512])
 {
     constexpr int TT = N / 8, E = env_e<N>(), TE = N / E, NW = N / 512;
-    constexpr int TWM = E == 8 ? TW_LFT : TW_TABLE;
+    constexpr int TWM = E == 8 ? TW_LFR : TW_TABLE;
     constexpr bool WAVE = NW == 1;
     // opaque, so that none of this path's addresses are computed ahead of the
     // caller's loop and held in registers through it
     int t = threadIdx.x;
     asm volatile("" : "+v"(t));
+    C2<T> w[tw_count<N, E, E, TWM>()];
+    if (t < TE) load_twiddles<T, N, E, E, TWM, +1>(w, tw, t);
     for (int i = t; i < N; i += TT) la[lpad<T>(i)] = C2<T>{0, 0};
     lds_sync<WAVE>();
     for (unsigned j = t; j < nb; j += TT) stage_bin<T, N>(la, k_lo + j, Md[j], Xs[j]);
@@ -1887,8 +1892,8 @@ __device__ __attribute__((noinline)) void env_redo(const XBin<T>* __restrict__ X
     T bv[3] = {(T)-1, (T)-1, (T)-1};
     int bi[3] = {0, 0, 0};
     if (t < TE) {  // (all threads where the transform has workgroup barriers)
-        fft<T, N, E, +1, TWM, E, WAVE>(x, la, tw, t);
-        fft<T, N, E, +1, TWM, E, WAVE>(xh, la, tw, t);
+        fft<T, N, E, +1, TWM, E, WAVE>(x, la, tw, t, w);
+        fft<T, N, E, +1, TWM, E, WAVE>(xh, la, tw, t, w);
 #pragma unroll
         for (int i = 0; i < E; ++i) {
             const T p0 = x[i].re * x[i].re + xh[i].re * xh[i].re;
@@ -1972,7 +1977,7 @@ __device__ __forceinline__ void env_maxima(const T (&pt)[8], const T (&pp)[8], i
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         if (c < c_lo) continue;
-        const unsigned thr = env_near_key<T>(top[c], top[2]);
+        const unsigned thr = env_near_key<T>(top[c], top[2], c == 2);
         if (__ballot(mine[c] >= thr) == 0ull) continue;  // no lane of this wave
         unsigned n_near = 0;
         int at_r = 8;
@@ -2022,9 +2027,10 @@ __device__ __forceinline__ void env_bins(const MBin<T> (&mb)[2], const XBin<T> (
 // workgroups, at most what the device holds): XCD x = block mod 8 takes the
 // x-th eighth, its workgroups stride through it side by side, so that at any
 // time an XCD works on one or two directions and their coefficient rows stay
-// in its L2.  One event: u = direction * S + station.  Many events (sunits[u] =
-// (event, station), one direction each): the peaks of u go to rows 3 u, and
-// an event whose skip flag is set is passed over.
+// in its L2.  One event: u = direction * S + station.  MANY events (sunits[u] =
+// (event, station), one direction each; spectra rows in that order, coefficient
+// rows by event, one band): the peaks of u go to rows 3 u, and an event whose
+// skip flag is set is passed over.
 //
 // Bound by VALU issue: about 610 instructions per wave and station in float
 // (468 of them the two transforms, at 3 per point and radix-2 level), of which
@@ -2037,15 +2043,15 @@ __device__ __forceinline__ void env_bins(const MBin<T> (&mb)[2], const XBin<T> (
 template <typename T, int N>
 constexpr int env_peaks_min_waves() { return sizeof(T) == 8 || N == 512 ? 4 : 6; }
 
-template <typename T, int N>
+template <typename T, int N, bool MANY>
 __global__ __launch_bounds__(N / 8) __attribute__((amdgpu_waves_per_eu(env_peaks_min_waves<T, N>()))) void k_env_peaks(
     EvDesc ev0, int64_t n_su, const XBin<T>* __restrict__ X, const MBin<T>* __restrict__ M, T* __restrict__ peak,
     int* __restrict__ arg, const C2<T>* __restrict__ tw, const int* __restrict__ skip,
-    const EvDesc* __restrict__ evs, const int2* __restrict__ sunits, int skip_stride, int total_only)
+    const int2* __restrict__ sunits, int skip_stride, int total_only)
 {
     constexpr int TT = N / 8, NW = N / 512;
     constexpr bool WAVE = NW == 1;
-    if (sunits == nullptr && skip != nullptr && skip[0]) return;  // set by a converged reconstruction loop
+    if (!MANY && skip != nullptr && skip[0]) return;  // set by a converged reconstruction loop
     __shared__ C2<T> la[qb_elems<N>()];
     __shared__ T red_v[3][NW];
     __shared__ int red_i[3][NW];
@@ -2060,41 +2066,34 @@ __global__ __launch_bounds__(N / 8) __attribute__((amdgpu_waves_per_eu(env_peaks
     const int64_t xcd = blockIdx.x & 7, u_end = n_su * (xcd + 1) / 8;
     int64_t u = n_su * xcd / 8 + (blockIdx.x >> 3);
     const int step = (int)(gridDim.x >> 3);
-    struct Su {
-        const XBin<T>* x;
-        const MBin<T>* m;
-        unsigned nb, k_lo;
-    };
-    auto locate = [&](int64_t uu) {
-        if (sunits != nullptr) {
-            const int2 es = sunits[uu];
-            const EvDesc& e = evs[es.x];
-            return Su{X + e.x_off + (int64_t)es.y * e.nb, M + e.m_off, (unsigned)e.nb, (unsigned)e.k_lo};
-        }
-        const int64_t d = uu / ev0.S;
-        const int64_t s = uu - d * ev0.S;
-        return Su{X + s * ev0.nb, M + d * ev0.nb, (unsigned)ev0.nb, (unsigned)ev0.k_lo};
-    };
-    // (one event: the direction and station of u, stepped without a division)
+    const unsigned nb = (unsigned)ev0.nb, k_lo = (unsigned)ev0.k_lo;
+    // (one event: the direction and station of u, stepped without a division;
+    // many: the next station's event, read one station ahead)
     const int S1 = max(ev0.S, 1);
     const int d_step = step / S1, s_step = step - d_step * S1;
-    int64_t d_at = u / S1;
+    int64_t d_at = n_su >> 32 ? u / S1 : (int64_t)((unsigned)u / (unsigned)S1);
     int s_at = (int)(u - d_at * S1);
+    int e_next = MANY && u < u_end ? sunits[u].x : 0;
     vmem_wait_all();
     lds_sync<WAVE>();
     while (u < u_end) {
         const int64_t u_first = u;
         for (int it = 0; it < kEnvRound && u < u_end; ++it, u += step) {
-            Su su;
-            if (sunits != nullptr) {
-                if (skip != nullptr && skip[(int64_t)sunits[u].x * skip_stride]) continue;
-                su = locate(u);
+            const XBin<T>* xs;
+            const MBin<T>* ms;
+            if constexpr (MANY) {
+                const int e = e_next;
+                if (u + step < u_end) e_next = sunits[u + step].x;
+                if (skip != nullptr && skip[(int64_t)e * skip_stride]) continue;
+                xs = X + u * nb;
+                ms = M + (int64_t)e * nb;
             } else {
-                su = Su{X + (int64_t)s_at * ev0.nb, M + d_at * ev0.nb, (unsigned)ev0.nb, (unsigned)ev0.k_lo};
+                xs = X + (int64_t)s_at * nb;
+                ms = M + d_at * nb;
                 d_at += d_step;
                 s_at += s_step;
-                if (s_at >= ev0.S) {
-                    s_at -= ev0.S;
+                if (s_at >= S1) {
+                    s_at -= S1;
                     ++d_at;
                 }
             }
@@ -2102,8 +2101,8 @@ __global__ __launch_bounds__(N / 8) __attribute__((amdgpu_waves_per_eu(env_peaks
             // band: the loads are out of the rows' range)
             C2<T> at[2], ap[2];
             {
-                const __amdgpu_buffer_rsrc_t xr = buffer_range(su.x, su.nb * (unsigned)sizeof(XBin<T>));
-                const __amdgpu_buffer_rsrc_t mr = buffer_range(su.m, su.nb * (unsigned)sizeof(MBin<T>));
+                const __amdgpu_buffer_rsrc_t xr = buffer_range(xs, nb * (unsigned)sizeof(XBin<T>));
+                const __amdgpu_buffer_rsrc_t mr = buffer_range(ms, nb * (unsigned)sizeof(MBin<T>));
                 XBin<T> xb[2];
                 MBin<T> mb[2];
 #pragma unroll
@@ -2112,7 +2111,7 @@ __global__ __launch_bounds__(N / 8) __attribute__((amdgpu_waves_per_eu(env_peaks
                     xb[k] = load_record<XBin<T>>(xr, j);
                     mb[k] = load_record<MBin<T>>(mr, j);
                 }
-                env_bins<T, N>(mb, xb, su.k_lo, t, at, ap);
+                env_bins<T, N>(mb, xb, k_lo, t, at, ap);
             }
             qb_pin(q);
             C2<T> x[8];
@@ -2142,8 +2141,9 @@ __global__ __launch_bounds__(N / 8) __attribute__((amdgpu_waves_per_eu(env_peaks
                 const int it = __builtin_ctzll(redo);
                 redo &= redo - 1;
                 const int64_t uu = u_first + (int64_t)it * step;
-                const Su su = locate(uu);
-                env_redo<T, N, 0>(su.x, su.m, su.nb, su.k_lo, peak + 3 * uu, arg + 3 * uu,
+                const int64_t row = MANY ? uu : uu % S1;
+                const int64_t dir = MANY ? sunits[uu].x : uu / S1;
+                env_redo<T, N, 0>(X + row * nb, M + dir * nb, nb, k_lo, peak + 3 * uu, arg + 3 * uu,
                                (unsigned)__builtin_amdgcn_readlane((int)todo, it), la, tw, red_v, red_i);
             } while (redo != 0ull);
             // (again, so that they are not held in registers meanwhile)
@@ -4004,14 +4004,14 @@ static int env_spw(int S, int64_t n_dir)
 
 // Workgroups of k_env_peaks the device holds at once, a multiple of 8 (cached;
 // 512 if unknown).
-template <typename T, int N>
+template <typename T, int N, bool MANY>
 static int env_peaks_blocks()
 {
     static const int blocks = [] {
         int dev = 0, cus = 0, occ = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_env_peaks<T, N>, N / 8, 0) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_env_peaks<T, N, MANY>, N / 8, 0) != hipSuccess ||
             cus * occ < 8)
             return 512;
         return cus * occ / 8 * 8;
@@ -4045,9 +4045,14 @@ static hipError_t launch_env_n(hipStream_t st, const EvDesc& ev0, int spw, int n
 {
     if constexpr (N >= 512) {
         if (efield == nullptr && env_peaks_applies(sizeof(T) == 4, N, ev0.nb, scores)) {
-            const int64_t grid = std::min<int64_t>((n_su + 7) / 8 * 8, env_peaks_blocks<T, N>());
-            hipLaunchKernelGGL((k_env_peaks<T, N>), dim3((unsigned)grid), dim3(N / 8), 0, st, ev0, n_su, X, M, peak,
-                               arg, tw, skip, evs, sunits, skip_stride, total_only ? 1 : 0);
+            const int64_t resident = sunits ? env_peaks_blocks<T, N, true>() : env_peaks_blocks<T, N, false>();
+            const dim3 grid((unsigned)std::min<int64_t>((n_su + 7) / 8 * 8, resident)), block(N / 8);
+            if (sunits)
+                hipLaunchKernelGGL((k_env_peaks<T, N, true>), grid, block, 0, st, ev0, n_su, X, M, peak, arg, tw, skip,
+                                   sunits, skip_stride, total_only ? 1 : 0);
+            else
+                hipLaunchKernelGGL((k_env_peaks<T, N, false>), grid, block, 0, st, ev0, n_su, X, M, peak, arg, tw,
+                                   skip, sunits, skip_stride, total_only ? 1 : 0);
             return hipGetLastError();
         }
     }
@@ -4345,25 +4350,27 @@ __global__ __launch_bounds__(kBlock) void k_recon_step(int it, int last, int S, 
     recon_step_block(blockIdx.x, it, last, S, dt_ns, pos, env_arg, hist, dirs, cur, state, ev_st, Stot, max_iter);
 }
 
-// One event's step `it` (not the last) and, unless it stopped the loop, the
-// coefficient rows of the direction it produced: the step's two
-// single-workgroup launches (k_recon_step, then k_coef of one direction
-// skipped on the stop flag) as one.  The step's thread 0 writes the direction
-// and the flag before the barrier that precedes the coefficients' reads.
+// Step `it` (not the last) of every event, a workgroup each, and, unless it
+// stopped the event's loop, the coefficient rows of the direction it produced:
+// the step's thread 0 writes the direction and the flag before the barrier that
+// precedes the coefficients' reads.  One launch instead of k_recon_step and
+// k_coef, each of which costs 5-10 us for a few of work.
 template <typename Tt, typename T>
 __global__ __launch_bounds__(kBlock) void k_recon_step_coef(int it, int S, double dt_ns,
                                                              const double* __restrict__ pos,
                                                              const int* __restrict__ env_arg,
                                                              int* __restrict__ hist, double* dirs, double* cur,
-                                                             int* state, int max_iter,
-                                                             const C2<Tt>* __restrict__ nodes, GridDev gd,
-                                                             EvDesc ev0, int64_t fs, double fallback_rel,
+                                                             int* state, const int2* __restrict__ ev_st, int Stot,
+                                                             int max_iter, const C2<Tt>* __restrict__ nodes,
+                                                             GridDev gd, EvDesc ev0, int64_t fs, double fallback_rel,
                                                              double singular_rel, MBin<T>* __restrict__ M)
 {
-    recon_step_block(0, it, 0, S, dt_ns, pos, env_arg, hist, dirs, cur, state, nullptr, S, max_iter);
+    const int e = blockIdx.x;
+    recon_step_block(e, it, 0, S, dt_ns, pos, env_arg, hist, dirs, cur, state, ev_st, Stot, max_iter);
     __syncthreads();
-    coef_block<Tt, T, false>(0, nodes, gd, ev0, nullptr, nullptr, cur, 0.0, 0.0, fs, fallback_rel, singular_rel, M,
-                             nullptr, 0.0, state, 0);
+    // (rows and directions of event e: direction e of the one descriptor)
+    coef_block<Tt, T, false>(e, nodes, gd, ev0, nullptr, nullptr, cur, 0.0, 0.0, fs, fallback_rel, singular_rel, M,
+                             nullptr, 0.0, state + 4 * e, 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -4661,12 +4668,14 @@ static au_status run_reconstruct(const au_table* tb, const au_event* ev, const E
         } else if (op % 2 == 0) {
             if (tb->dtype == AU_F64)
                 hipLaunchKernelGGL((k_recon_step_coef<double, T>), dim3(1), dim3(kBlock), 0, st, it, p.S, dt_ns,
-                                   (const double*)pos, (const int*)arg, hist, dirs, cur, state, max_iter,
+                                   (const double*)pos, (const int*)arg, hist, dirs, cur, state,
+                                   (const int2*)nullptr, p.S, max_iter,
                                    (const C2<double>*)tb->d_nodes, tb->g, ev0, ev->fs_hz, ev->fallback_rel,
                                    ev->singular_rel, M);
             else
                 hipLaunchKernelGGL((k_recon_step_coef<float, T>), dim3(1), dim3(kBlock), 0, st, it, p.S, dt_ns,
-                                   (const double*)pos, (const int*)arg, hist, dirs, cur, state, max_iter,
+                                   (const double*)pos, (const int*)arg, hist, dirs, cur, state,
+                                   (const int2*)nullptr, p.S, max_iter,
                                    (const C2<float>*)tb->d_nodes, tb->g, ev0, ev->fs_hz, ev->fallback_rel,
                                    ev->singular_rel, M);
         } else {
@@ -5064,8 +5073,10 @@ extern "C" au_status au_direction_fit(const au_table* tb, const au_event* ev, co
 
 namespace {
 
+// Results (state, directions, times) and inputs (positions, descriptors and work
+// lists) each lie together, so that each goes in one copy.
 struct BatchReconLayout {
-    size_t x, m, hist, dirs, cur, state, pos, peak, arg, evs, sunits, cunits, eunits, evst, total;
+    size_t x, m, state, dirs, hist, cur, peak, arg, pos, evs, sunits, eunits, evst, total;
 };
 
 BatchReconLayout batch_recon_layout(int prec, int64_t stot, int n_events, int nb, int max_iter, int64_t n_eunits)
@@ -5074,20 +5085,19 @@ BatchReconLayout batch_recon_layout(int prec, int64_t stot, int n_events, int nb
     BatchReconLayout r;
     r.x = align256((size_t)stot * nb * 4 * tsz + 1);
     r.m = align256((size_t)n_events * nb * 8 * tsz + 1);
-    r.hist = align256((size_t)(max_iter + 1) * stot * sizeof(int32_t));
-    r.dirs = align256((size_t)n_events * max_iter * 2 * sizeof(double));
-    r.cur = align256((size_t)n_events * 2 * sizeof(double));
     r.state = align256((size_t)n_events * 4 * sizeof(int32_t));
-    r.pos = align256((size_t)stot * 2 * sizeof(double));
+    r.dirs = align256((size_t)n_events * max_iter * 2 * sizeof(double));
+    r.hist = align256((size_t)(max_iter + 1) * stot * sizeof(int32_t));
+    r.cur = align256((size_t)n_events * 2 * sizeof(double));
     r.peak = align256((size_t)stot * 3 * tsz);
     r.arg = align256((size_t)stot * 3 * sizeof(int32_t));
+    r.pos = align256((size_t)stot * 2 * sizeof(double));
     r.evs = align256((size_t)n_events * sizeof(EvDesc));
     r.sunits = align256((size_t)stot * sizeof(int2));
-    r.cunits = align256((size_t)n_events * sizeof(int2));
     r.eunits = align256((size_t)n_eunits * sizeof(int4));
     r.evst = align256((size_t)n_events * sizeof(int2));
-    r.total = r.x + r.m + r.hist + r.dirs + r.cur + r.state + r.pos + r.peak + r.arg + r.evs + r.sunits +
-              r.cunits + r.eunits + r.evst;
+    r.total = r.x + r.m + r.state + r.dirs + r.hist + r.cur + r.peak + r.arg + r.pos + r.evs + r.sunits + r.eunits +
+              r.evst;
     return r;
 }
 
@@ -5134,24 +5144,26 @@ static au_status run_reconstruct_batch(const au_table* tb, const au_event* ev, c
     unsigned char* q = (unsigned char*)d_work;
     XBin<T>* X = (XBin<T>*)q;
     MBin<T>* M = (MBin<T>*)(q += r.x);
-    int* hist = (int*)(q += r.m);
-    double* dirs = (double*)(q += r.hist);
-    double* cur = (double*)(q += r.dirs);
-    int* state = (int*)(q += r.cur);
-    double* pos = (double*)(q += r.state);
-    T* peak = (T*)(q += r.pos);
+    int* state = (int*)(q += r.m);
+    double* dirs = (double*)(q += r.state);
+    int* hist = (int*)(q += r.dirs);
+    double* cur = (double*)(q += r.hist);
+    T* peak = (T*)(q += r.cur);
     int* arg = (int*)(q += r.peak);
-    EvDesc* evs = (EvDesc*)(q += r.arg);
+    double* pos = (double*)(q += r.arg);
+    EvDesc* evs = (EvDesc*)(q += r.pos);
     int2* sunits = (int2*)(q += r.evs);
-    int2* cunits = (int2*)(q += r.sunits);
-    int4* eunits = (int4*)(q += r.cunits);
+    int4* eunits = (int4*)(q += r.sunits);
     int2* evst = (int2*)(q += r.eunits);
-    // descriptors, built on the host and copied once
-    std::vector<EvDesc> hevs((size_t)n_events);
-    std::vector<int2> hsu((size_t)stot), hcu((size_t)n_events), hst((size_t)n_events);
-    std::vector<int4> heu;
-    heu.reserve((size_t)n_eunits);
-    int64_t so = 0;
+    // positions, descriptors and work lists, built on the host as they lie in the
+    // workspace and copied once
+    std::vector<unsigned char> up(r.pos + r.evs + r.sunits + r.eunits + r.evst);
+    std::memcpy(up.data(), h_pos, sizeof(double) * 2 * stot);
+    EvDesc* hevs = (EvDesc*)(up.data() + r.pos);
+    int2* hsu = (int2*)((unsigned char*)hevs + r.evs);
+    int4* heu = (int4*)((unsigned char*)hsu + r.sunits);
+    int2* hst = (int2*)((unsigned char*)heu + r.eunits);
+    int64_t so = 0, eu = 0;
     for (int32_t e = 0; e < n_events; ++e) {
         EvDesc d{};
         d.volt_off = h_voff[e];
@@ -5164,19 +5176,13 @@ static au_status run_reconstruct_batch(const au_table* tb, const au_event* ev, c
         d.D = 1;
         d.k_lo = p.k_lo;
         d.nb = p.nb;
-        hevs[(size_t)e] = d;
-        for (int s = 0; s < h_ns[e]; ++s) hsu[(size_t)(so + s)] = int2{e, s};
-        for (int s0 = 0; s0 < h_ns[e]; s0 += spw) heu.push_back(int4{e, 0, s0, std::min((int)h_ns[e], s0 + spw)});
-        hcu[(size_t)e] = int2{e, 0};
-        hst[(size_t)e] = int2{(int)so, h_ns[e]};
+        hevs[e] = d;
+        for (int s = 0; s < h_ns[e]; ++s) hsu[so + s] = int2{e, s};
+        for (int s0 = 0; s0 < h_ns[e]; s0 += spw) heu[eu++] = int4{e, 0, s0, std::min((int)h_ns[e], s0 + spw)};
+        hst[e] = int2{(int)so, h_ns[e]};
         so += h_ns[e];
     }
-    HIP_TRY(hipMemcpyAsync(evs, hevs.data(), hevs.size() * sizeof(EvDesc), hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(sunits, hsu.data(), hsu.size() * sizeof(int2), hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(cunits, hcu.data(), hcu.size() * sizeof(int2), hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(eunits, heu.data(), heu.size() * sizeof(int4), hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(evst, hst.data(), hst.size() * sizeof(int2), hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(pos, h_pos, sizeof(double) * 2 * stot, hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(pos, up.data(), up.size(), hipMemcpyHostToDevice, st));
     // (each event's state is cleared by its first step)
     EvDesc ev0{};
     ev0.N = p.N;
@@ -5191,42 +5197,66 @@ static au_status run_reconstruct_batch(const au_table* tb, const au_event* ev, c
         e = launch_spectrum<float, T>(p.N, st, (const float*)d_volt, ev0, evs, sunits, (int)stot, p.nb, X, tw, hist);
     if (e != hipSuccess) return fail(AU_EDEVICE, std::string("spectrum/timing: ") + hipGetErrorString(e));
     const double dt_ns = 1e9 / (double)ev->fs_hz;
-    for (int it = 0; it <= max_iter; ++it) {
-        const int last = it == max_iter;
-        hipLaunchKernelGGL(k_recon_step, dim3(n_events), dim3(kBlock), 0, st, it, last, 0, dt_ns, (const double*)pos,
-                           (const int*)arg, hist, dirs, cur, state, (const int2*)evst, (int)stot, max_iter);
-        if (last) break;
-        if (tb->dtype == AU_F64)
-            launch_coef<double, T>(st, tb, ev0, evs, cunits, n_events, cur, 0, 0, ev->fs_hz, ev->fallback_rel,
-                                   ev->singular_rel, M, nullptr, (const int*)state, 4);
+    // Step `it` with the coefficients of its directions (the last one, after
+    // max_iter passes, tests convergence alone).  An event that has stopped makes
+    // its later work a no-op; the results are read after the step that follows
+    // two passes (the usual number) and then after every four more, until every
+    // event has stopped.
+    auto step = [&](int it) -> au_status {
+        if (it == max_iter)
+            hipLaunchKernelGGL(k_recon_step, dim3(n_events), dim3(kBlock), 0, st, it, 1, 0, dt_ns, (const double*)pos,
+                               (const int*)arg, hist, dirs, cur, state, (const int2*)evst, (int)stot, max_iter);
+        else if (tb->dtype == AU_F64)
+            hipLaunchKernelGGL((k_recon_step_coef<double, T>), dim3(n_events), dim3(kBlock), 0, st, it, 0, dt_ns,
+                               (const double*)pos, (const int*)arg, hist, dirs, cur, state, (const int2*)evst,
+                               (int)stot, max_iter, (const C2<double>*)tb->d_nodes, tb->g, ev0, ev->fs_hz,
+                               ev->fallback_rel, ev->singular_rel, M);
         else
-            launch_coef<float, T>(st, tb, ev0, evs, cunits, n_events, cur, 0, 0, ev->fs_hz, ev->fallback_rel,
-                                  ev->singular_rel, M, nullptr, (const int*)state, 4);
-        switch (p.N) {
+            hipLaunchKernelGGL((k_recon_step_coef<float, T>), dim3(n_events), dim3(kBlock), 0, st, it, 0, dt_ns,
+                               (const double*)pos, (const int*)arg, hist, dirs, cur, state, (const int2*)evst,
+                               (int)stot, max_iter, (const C2<float>*)tb->d_nodes, tb->g, ev0, ev->fs_hz,
+                               ev->fallback_rel, ev->singular_rel, M);
+        e = hipGetLastError();
+        return e == hipSuccess ? AU_OK
+                               : fail(AU_EDEVICE, std::string("reconstruction step: ") + hipGetErrorString(e));
+    };
+    au_status s = step(0);
+    if (s != AU_OK) return s;
+    std::vector<unsigned char> down;
+    for (int it = 0, upto = std::min(2, max_iter);; upto = std::min(upto + 4, max_iter)) {
+        for (; it < upto; ++it) {
+            switch (p.N) {
 #define X_(NN)                                                                                          \
     case NN:                                                                                            \
         e = launch_env_n<T, NN>(st, ev0, spw, (int)n_eunits, stot, X, M, (T*)nullptr, peak, arg, tw,    \
                                 (const int*)state, (const EvDesc*)evs, (const int2*)sunits,             \
                                 (const int4*)eunits, 4, true);                                          \
         break;
-            AU_FOR_EACH_N(X_)
+                AU_FOR_EACH_N(X_)
 #undef X_
-            default: e = hipErrorInvalidValue;
+                default: e = hipErrorInvalidValue;
+            }
+            if (e != hipSuccess) return fail(AU_EDEVICE, std::string("reconstruction pass: ") + hipGetErrorString(e));
+            s = step(it + 1);
+            if (s != AU_OK) return s;
         }
-        if (e != hipSuccess) return fail(AU_EDEVICE, std::string("reconstruction step: ") + hipGetErrorString(e));
+        // states, directions and the rows of times so far
+        const size_t rows = sizeof(int32_t) * (size_t)(it + 1) * stot;
+        down.resize(r.state + r.dirs + rows);
+        HIP_TRY(hipMemcpyAsync(down.data(), state, down.size(), hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        const int32_t* hstate = (const int32_t*)down.data();
+        bool stopped = true;
+        for (int32_t k = 0; k < n_events; ++k) stopped = stopped && hstate[4 * (size_t)k] != 0;
+        if (!stopped && it < max_iter) continue;
+        std::memcpy(h_dirs, down.data() + r.state, sizeof(double) * 2 * max_iter * (size_t)n_events);
+        std::memcpy(h_times, down.data() + r.state + r.dirs, rows);
+        for (int32_t k = 0; k < n_events; ++k) {
+            h_n_dirs[k] = hstate[4 * (size_t)k + 1];
+            h_converged[k] = hstate[4 * (size_t)k + 3] ? -1 : hstate[4 * (size_t)k + 2];
+        }
+        return AU_OK;
     }
-    std::vector<int32_t> hstate((size_t)n_events * 4);
-    HIP_TRY(hipMemcpyAsync(hstate.data(), state, sizeof(int32_t) * 4 * n_events, hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipMemcpyAsync(h_dirs, dirs, sizeof(double) * 2 * max_iter * (size_t)n_events, hipMemcpyDeviceToHost,
-                           st));
-    HIP_TRY(hipMemcpyAsync(h_times, hist, sizeof(int32_t) * (size_t)(max_iter + 1) * stot, hipMemcpyDeviceToHost,
-                           st));
-    HIP_TRY(hipStreamSynchronize(st));
-    for (int32_t k = 0; k < n_events; ++k) {
-        h_n_dirs[k] = hstate[4 * (size_t)k + 1];
-        h_converged[k] = hstate[4 * (size_t)k + 3] ? -1 : hstate[4 * (size_t)k + 2];
-    }
-    return AU_OK;
 }
 
 extern "C" au_status au_reconstruct_batch_workspace_bytes(const au_table* tb, const au_event* ev, int32_t n_events,

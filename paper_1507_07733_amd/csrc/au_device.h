@@ -350,14 +350,12 @@ constexpr int lds_zero_slot() { return N + 1; }
 //             wavefront (fft4096_xw): one through the wavefront's own LDS
 //             slots with no workgroup barrier, one as a register transpose;
 //             one workgroup exchange per transform instead of three.
-//   TW_LFT:   the TW_LF pairs read from the table each time (fft only; the
-//             envelope kernel's rare path, which has no registers set aside).
-enum { TW_TABLE = 0, TW_REG = 1, TW_SPLIT = 2, TW_HYB = 3, TW_LF = 4, TW_LFR = 5, TW_LFW = 6, TW_LFT = 7 };
+enum { TW_TABLE = 0, TW_REG = 1, TW_SPLIT = 2, TW_HYB = 3, TW_LF = 4, TW_LFR = 5, TW_LFW = 6 };
 
 // Twiddles of the early passes in a per-workgroup LDS table.
 constexpr bool tw_lds_early(int mode) { return mode == TW_HYB || mode == TW_LF; }
 // Fused multiply-add butterflies with (tangent, cosine) twiddle pairs.
-constexpr bool tw_lf(int mode) { return mode == TW_LF || mode == TW_LFR || mode == TW_LFW || mode == TW_LFT; }
+constexpr bool tw_lf(int mode) { return mode == TW_LF || mode == TW_LFR || mode == TW_LFW; }
 // Every pass's twiddles in registers.
 constexpr bool tw_all_reg(int mode) { return mode == TW_REG || mode == TW_LFR || mode == TW_LFW; }
 // (tangent, cosine) pairs per butterfly of a radix-R pass in TW_LF, TW_LFR, TW_LFW.
@@ -608,9 +606,7 @@ __device__ __forceinline__ void fft_pass(C2<T> (&x)[E], C2<T>* __restrict__ lds,
             C2<T> L[LE];
 #pragma unroll
             for (int e = 0; e < LE; ++e) {
-                if constexpr (TWMODE == TW_LFT)
-                    L[e] = lf_tab<SIGN>(tw, k * (kTwN / (NS * R)), e);
-                else if constexpr (TWMODE == TW_LF && NS < TT)
+                if constexpr (TWMODE == TW_LF && NS < TT)
                     L[e] = lf_sign<SIGN>(ltw[ltw_offset<N, E, RMAX, TW_LF>(NS) + e * NS + k]);
                 else
                     L[e] = lf_sign<SIGN>(w[OFF + m * LE + e]);
