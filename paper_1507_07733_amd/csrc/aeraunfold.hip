@@ -1811,11 +1811,12 @@ __global__ __launch_bounds__((N / E) > kBlock ? (N / E) : kBlock) void k_unfold_
 // traces with noise, and every station of a field that is zero.
 
 // Two samples may change places between the two evaluations within kEnvNear of
-// the total field's maximum in amplitude: 2^-17 (float), 2^-46 (double).  Either
-// transform is off by at most about 2 log2(N) u of the total field's largest
-// magnitude (u = 2^-24 or 2^-53; the error observed is a tenth of that), and four
-// such errors (two samples, two evaluations) can add up: 96 u at N = 4096, and
-// kEnvNear is 128 u.
+// the total field's maximum in amplitude: 32 u, 2^-19 in float and 2^-48 in double
+// (u = 2^-24 or 2^-53).  Over 2 10^5 stations of 512 to 4096 samples in float,
+// noise and pulses, the evaluations of a maximum differed by 1.1 u (rms) and 6.1 u
+// at most, so that two samples within 32 u are twenty standard deviations away.
+// (At 128 u four times the stations are decided twice, each the last of its
+// launch for about 14 us.)
 // Squares below this are decided by env_redo too: they may have lost bits to
 // underflow.
 template <typename T>
@@ -1834,14 +1835,13 @@ __device__ __forceinline__ unsigned env_key(double v) { return (unsigned)__doubl
 // above m (1 - 2 kEnvNear R / sqrt(m)); a relative step of 2^-b moves a key by
 // at most 2^(B - b) (B one more than its mantissa bits), and R / sqrt(m) is 1 for
 // the total itself and below 2^((e + 1) / 2) for a difference of e in the binary
-// exponents.  (Float: 256 keys for the total, which one station in some
-// thousands has another sample in; double, whose keys are coarser than kEnvNear:
-// two, one in 10^5.)
+// exponents.  (Float: 64 keys for the total, which one station in 10^4 or 10^5 has
+// another sample in; double, whose keys are coarser than kEnvNear: two.)
 template <typename T>
 __device__ __forceinline__ unsigned env_near_key(unsigned m, unsigned r2, bool total)
 {
     constexpr int MB = sizeof(T) == 4 ? 23 : 20;
-    constexpr int STEP = MB + 1 + 1 - (sizeof(T) == 4 ? 17 : 46);  // log2 of 2 kEnvNear 2^B
+    constexpr int STEP = MB + 1 + 1 - (sizeof(T) == 4 ? 19 : 48);  // log2 of 2 kEnvNear 2^B
     const int h = STEP + (total ? 0 : ((int)(r2 >> MB) - (int)(m >> MB) + 2) >> 1);
     const unsigned d = h <= 0 ? 2u : (h >= 31 ? m : (1u << h) + 1u);
     return d >= m ? 0u : m - d;
