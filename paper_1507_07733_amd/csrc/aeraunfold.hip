@@ -700,12 +700,12 @@ __device__ __forceinline__ void touch(const C2<T>& v)
 
 // One in-band bin of the packed spectrum: Z[k] = E_theta + i E_phi and
 // Z[N-k] = conj E_theta + i conj E_phi (only the real parts at k = 0).
-// (XW: in the digit-reversed slots of the 4096-point in-wave transform)
+// (XW: in the digit-reversed slots of the transform with in-wave exchanges)
 template <typename T, int N, bool XW = false>
 __device__ __forceinline__ int stage_slot(unsigned k)
 {
     if constexpr (XW)
-        return xw_slot(xw_pos((int)k));
+        return xw_slot<N>(xw_pos<N>((int)k));
     else
         return lpad<T>((int)k);
 }
@@ -750,6 +750,11 @@ constexpr int unfold_min_waves()
     return 1;
 }
 
+// FFT groups per workgroup: one where the exchanges inside the wavefront leave
+// little to share (and addresses stay uniform), else as many as fill a block.
+template <typename T, int N, int E, int TWMODE, bool PP>
+constexpr int unfold_groups() { return TWMODE == TW_LFW ? 1 : groups_per_block<T, N, E, PP ? 2 : 1>(); }
+
 template <typename T, int N, int E, int RMAX, int TWMODE, bool WAVE, bool PAIR, bool PP>
 __global__ __launch_bounds__((N / E) > kBlock ? (N / E) : kBlock)
 __attribute__((amdgpu_waves_per_eu(unfold_min_waves<T, E, TWMODE, PAIR, PP>()))) void k_unfold(EvDesc ev0, const EvDesc* __restrict__ evs,
@@ -762,19 +767,20 @@ __attribute__((amdgpu_waves_per_eu(unfold_min_waves<T, E, TWMODE, PAIR, PP>())))
                                                    const int* __restrict__ xcd_off)
 {
     constexpr int TT = N / E;
-    constexpr int G = groups_per_block<T, N, E, PP ? 2 : 1>();
+    constexpr int G = unfold_groups<T, N, E, TWMODE, PP>();
     // bins per thread prefetched for the next station: the FP32 shapes whose
     // early twiddles live in LDS have the registers for it; in FP64 the
     // two-buffer shape, at two waves per SIMD (one workgroup per CU, which
     // its LDS allows anyway)
     constexpr int PF = ((tw_lds_early(TWMODE) || TWMODE == TW_LFR || TWMODE == TW_LFW) && E <= 8 && !PAIR && !WAVE &&
                         (sizeof(T) == 4 || PP)) ? AU_UNFOLD_PF : 0;
-    // the 4096-point transform with in-wavefront exchanges: the staging
+    // the transform with in-wavefront exchanges: the staging
     // writes the digit-reversed order it reads, the first buffer holds the
     // staging and the second its one exchange
     constexpr bool XW = TWMODE == TW_LFW;
-    static_assert(!XW || (N == 4096 && E == 8 && RMAX == 8 && PP && !PAIR && !WAVE && G == 1 && PF > 0),
-                  "in-wave exchanges: the 4096-point shape only");
+    constexpr int R2 = XW ? N / 512 : 1;
+    static_assert(!XW || (N >= 1024 && E == 8 && RMAX == 8 && PP && !PAIR && !WAVE && G == 1 && PF > 0),
+                  "in-wave exchanges: 8 values per thread, one group, two buffers");
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int sh_u;
     __shared__ int sh_list;
@@ -789,6 +795,7 @@ __attribute__((amdgpu_waves_per_eu(unfold_min_waves<T, E, TWMODE, PAIR, PP>())))
     C2<T>* ltw = reinterpret_cast<C2<T>*>(smem) + G * (PP ? 2 : 1) * lds_elems<N>();
     C2<T> w[tw_count<N, E, RMAX, TWMODE>()];
     load_twiddles<T, N, E, RMAX, TWMODE, +1>(w, tw, t);
+    if constexpr (XW && N < 4096) xw_load_last<T, N>(w, tw, t);
     if constexpr (tw_lds_early(TWMODE)) fill_lds_twiddles<T, N, E, RMAX, +1, TWMODE>(ltw, tw, threadIdx.x, blockDim.x);
     if constexpr (PF > 0) {  // (ordered by the barrier below)
         if (threadIdx.x < (PP ? 2 : 1) * G) zero_slot_clear<T, N>(smem, threadIdx.x);
@@ -871,7 +878,7 @@ __attribute__((amdgpu_waves_per_eu(unfold_min_waves<T, E, TWMODE, PAIR, PP>())))
             // barrier has passed.)
             if (k_lo != zb_klo || nb != zb_nb) {  // uniform
 #pragma unroll
-                for (int i = 0; i < E; ++i) lds[xw_slot(t + TT * i)] = C2<T>{0, 0};
+                for (int i = 0; i < E; ++i) lds[xw_slot<N>(t + TT * i)] = C2<T>{0, 0};
                 lds_barrier();
                 zb_klo = k_lo;
                 zb_nb = nb;
@@ -988,7 +995,7 @@ __attribute__((amdgpu_waves_per_eu(unfold_min_waves<T, E, TWMODE, PAIR, PP>())))
                     if constexpr (XW) {
                         // position t + TT i of the digit-reversed order; out
                         // of band it holds the zero written for the band
-                        x[i] = lds[xw_slot((int)(t + TT * i))];
+                        x[i] = lds[xw_slot<N>((int)(t + TT * i))];
                     } else {
                         const unsigned k = t + TT * i;
                         const unsigned kk = (k <= N / 2) ? k : N - k;
@@ -1008,7 +1015,7 @@ __attribute__((amdgpu_waves_per_eu(unfold_min_waves<T, E, TWMODE, PAIR, PP>())))
                 // staging in lds, both exchanges in lds2: the next station's
                 // staging writes lds after this station's exchange barrier,
                 // which every thread passes after its gathers from lds
-                fft4096_xw<T, +1>(x, lds2, w, t);
+                fft_xw<T, N, +1>(x, lds2, w, t);
             } else if constexpr (PP) {
                 fft_pp<T, N, E, +1, TWMODE, RMAX, WAVE>(x, lds2, lds, tw, t, w, ltw);
                 // exchanges this station: the staging one (lds, unless PAIR)
@@ -1041,11 +1048,12 @@ __attribute__((amdgpu_waves_per_eu(unfold_min_waves<T, E, TWMODE, PAIR, PP>())))
                 // trace base uniform
                 const __amdgpu_buffer_rsrc_t r = buffer_range(
                     efield + ev.efield_off + ((int64_t)d * ev.S + s) * 2 * N, 2 * N * (unsigned)sizeof(T));
-                const unsigned toff = (unsigned)t * (unsigned)sizeof(T);
+                const unsigned toff = (unsigned)(XW ? xw_out0<N>(t) : t) * (unsigned)sizeof(T);
 #pragma unroll
                 for (int i = 0; i < E; ++i) {
-                    buffer_store_nt(x[i].re, r, toff, (int)(TT * i * sizeof(T)));
-                    buffer_store_nt(x[i].im, r, toff, (int)((N + TT * i) * sizeof(T)));
+                    const int n = XW ? 64 * (i / R2) + 512 * (i % R2) : TT * i;
+                    buffer_store_nt(x[i].re, r, toff, (int)(n * sizeof(T)));
+                    buffer_store_nt(x[i].im, r, toff, (int)((N + n) * sizeof(T)));
                 }
             } else if (active) {
                 T* out = efield + ev.efield_off + ((int64_t)d * ev.S + s) * 2 * N;
@@ -1517,7 +1525,7 @@ __global__ __launch_bounds__((N / E) > kBlock ? (N / E) : kBlock) void k_unfold_
         if constexpr (XWE) {
             // the staging buffer's zeros (the staging writes in-band slots only)
 #pragma unroll
-            for (int i = 0; i < E; ++i) la[xw_slot(t + TT * i)] = C2<T>{0, 0};
+            for (int i = 0; i < E; ++i) la[xw_slot<N>(t + TT * i)] = C2<T>{0, 0};
         }
         lds_barrier();
     }
@@ -1617,7 +1625,7 @@ __global__ __launch_bounds__((N / E) > kBlock ? (N / E) : kBlock) void k_unfold_
                 // Zh = 0 at DC (thread 0, register 0)
 #pragma unroll
                 for (int i = 0; i < E; ++i) {
-                    x[i] = la[xw_slot(t + TT * i)];
+                    x[i] = la[xw_slot<N>(t + TT * i)];
                     xh[i] = i < E / 2 ? C2<T>{x[i].im, -x[i].re} : C2<T>{-x[i].im, x[i].re};
                 }
                 if (t == 0) xh[0] = C2<T>{0, 0};
@@ -1700,7 +1708,7 @@ __global__ __launch_bounds__((N / E) > kBlock ? (N / E) : kBlock) void k_unfold_
                 // every read of the Hilbert exchange in the first buffer is
                 // behind that barrier: its zeros back before the closing one
 #pragma unroll
-                for (int i = 0; i < E; ++i) la[xw_slot(t + TT * i)] = C2<T>{0, 0};
+                for (int i = 0; i < E; ++i) la[xw_slot<N>(t + TT * i)] = C2<T>{0, 0};
             }
             const int wv = t >> 6, lane = t & 63;
             const int cc = c_lo + wv;  // the component this wave reduces
@@ -2229,9 +2237,9 @@ constexpr bool variant_built(int n, int v, int tsize)
     // every pass's twiddle pairs in registers: FP64 (one workgroup per CU,
     // registers to spare); FP32 shapes need them for four waves per SIMD
     if (kUnfoldVariants[v].twmode == TW_LFR && tsize != 8) return false;
-    // the in-wavefront exchanges exist for the 4096-point transform only, in
-    // FP64 (the FP32 shape would spill at four waves per SIMD)
-    if (kUnfoldVariants[v].twmode == TW_LFW && (n != 4096 || tsize != 8)) return false;
+    // the in-wavefront exchanges: in FP64 (the FP32 shape would spill at four
+    // waves per SIMD)
+    if (kUnfoldVariants[v].twmode == TW_LFW && tsize != 8) return false;
     return true;
 }
 
@@ -2246,7 +2254,7 @@ struct UShape {
     static constexpr bool PP = kUnfoldVariants[V].pp;
     static constexpr int BUFS = PP ? 2 : 1;
     static constexpr int TT = N / E;
-    static constexpr int G = groups_per_block<T, N, E, BUFS>();
+    static constexpr int G = unfold_groups<T, N, E, TWMODE, PP>();
     static constexpr int BLOCK = G * TT;
     static constexpr size_t LDS =
         ((size_t)G * BUFS * lds_elems<N>() + (tw_lds_early(TWMODE) ? ltw_count<N, E, RMAX, TWMODE>() : 0)) *
@@ -2269,7 +2277,7 @@ static int ilog2(int n)
 // the hybrid table, at 1024 register twiddles; below, E=16 with register
 // twiddles for float and table twiddles for double).
 static std::mutex g_var_mu;
-static int g_variant[2][13] = {{1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 10, 12, 17},
+static int g_variant[2][13] = {{1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 17, 17, 17},
                                {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 12, 14, 14}};
 
 static int unfold_variant(int prec, int n)

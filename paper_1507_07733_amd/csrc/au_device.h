@@ -345,9 +345,9 @@ constexpr int lds_zero_slot() { return N + 1; }
 //   TW_LFR:   the TW_LF pairs of every pass in registers (no LDS table
 //             reads: for shapes with registers to spare whose transform is
 //             bound by LDS bandwidth, as FP64 at one workgroup per CU).
-//   TW_LFW:   TW_LFR's twiddles and butterflies in the 4096-point
-//             transform whose first two exchanges stay inside the
-//             wavefront (fft4096_xw): one through the wavefront's own LDS
+//   TW_LFW:   TW_LFR's twiddles and butterflies in the transform (1024
+//             to 4096 points) whose first two exchanges stay inside the
+//             wavefront (fft_xw): one through the wavefront's own LDS
 //             slots with no workgroup barrier, one as a register transpose;
 //             one workgroup exchange per transform instead of three.
 enum { TW_TABLE = 0, TW_REG = 1, TW_SPLIT = 2, TW_HYB = 3, TW_LF = 4, TW_LFR = 5, TW_LFW = 6 };
@@ -878,20 +878,33 @@ __device__ __forceinline__ void fft_pp(C2<T> (&x)[E], C2<T>* __restrict__ la, C2
 // 0-2 would take two (a DPP move and a select), so that transpose goes
 // through LDS, where a wavefront needs no barrier.
 
-// Slot of position q in the LDS buffers of fft4096_xw: an XOR of bits 0-2
-// with bits 6-8 (a permutation of each aligned block of 8 positions, so a
-// block of 512 stays in place), which keeps the gathers and the exchange (64
-// consecutive positions per wave) and the staging scatter (consecutive bins
-// k to positions 64 (k mod 8) + ...) free of bank conflicts for 8- and
+// The 1024- and 2048-point transforms have the same passes but the last, whose
+// radix R2 = N / 512 combines the R2 wavefronts' 512-point transforms: each
+// thread then runs 8 / R2 butterflies, of positions 64 (w 8 / R2 + b) + l.
+
+// Slot of position q in the staging buffer of fft_xw: an XOR of bits 0-2 with
+// the wave's bits and, below eight waves, with lane bits 3 and 4 (a permutation of
+// each aligned block of 8 positions), which keeps the gathers (64 consecutive
+// positions per wave) and the staging scatter (consecutive bins k to positions
+// 64 (k mod R2) + 8 ((k / R2) mod 8) + ...) free of bank conflicts for 8- and
 // 16-byte elements.
-__device__ __forceinline__ constexpr int xw_slot(int q) { return q ^ ((q >> 6) & 7); }
-// The digit-reversed input order in base-8 digits 0 and 2 of a 4096-point
-// index (an involution): element e sits at the gather position xw_pos(e) of
-// the thread and register pass 1 takes it from, and position q holds element
-// xw_pos(q).
+template <int N>
+__device__ __forceinline__ constexpr int xw_slot(int q)
+{
+    if constexpr (N == 4096) return q ^ ((q >> 6) & 7);
+    else if constexpr (N == 2048) return q ^ ((q >> 6) & 3) ^ (((q >> 3) & 1) << 2);
+    else return q ^ ((q >> 6) & 1) ^ (((q >> 3) & 3) << 1);
+}
+// Gather position of element e of the digit-reversed input: register r = e /
+// (N/8), and of the rest the wave takes the lowest digit (radix R2), lane bits
+// 3-5 the next, lane bits 0-2 the highest.
+template <int N>
 __device__ __forceinline__ constexpr int xw_pos(int e)
 {
-    return (e & 0xE38) | ((e & 7) << 6) | ((e >> 6) & 7);
+    if constexpr (N == 4096) return (e & 0xE38) | ((e & 7) << 6) | ((e >> 6) & 7);
+    constexpr int R2 = N / 512, TT = N / 8;
+    const int rem = e & (TT - 1);
+    return (e - rem) | ((rem & (R2 - 1)) << 6) | (((rem / R2) & 7) << 3) | (rem / (8 * R2));
 }
 
 // One transpose step of a pair of 32-bit words held in registers r0 and
@@ -975,23 +988,40 @@ __device__ __forceinline__ void xw_pass(C2<T> (&x)[8], const C2<T>* __restrict__
     }
 }
 
-// x[r] holds position t + 512 r of the digit-reversed input (see above);
-// returns x[r] = output element t + 512 r.  `la` is a buffer of
-// lds_elems<4096>() slots that no other thread group uses; the caller must
+// Samples of a thread's results after fft_xw: x[b R2 + i] = output element
+// xw_out0 + 64 b + 512 i.
+template <int N>
+__device__ __forceinline__ int xw_out0(int t) { return 64 * (8 / (N / 512)) * (t >> 6) + (t & 63); }
+
+// The twiddles of fft_xw's last pass (TW_LFR's place for them): positions 64 (w 8
+// / R2 + b) + l, radix R2 (at 4096 samples the ones load_twiddles has set).
+template <typename T, int N>
+__device__ __forceinline__ void xw_load_last(C2<T>* __restrict__ w, const C2<T>* __restrict__ tw, int t)
+{
+    constexpr int R2 = N / 512, LE = lf_entries(R2), OFF = tw_offset<N, 8, 8, TW_LFW>(512);
+#pragma unroll
+    for (int b = 0; b < 8 / R2; ++b)
+#pragma unroll
+        for (int e = 0; e < LE; ++e) w[OFF + b * LE + e] = lf_tab<+1>(tw, (xw_out0<N>(t) + 64 * b) * (8 / R2), e);
+}
+
+// x[r] holds position t + (N/8) r of the digit-reversed input (see above);
+// returns the outputs in xw_out0's order.  `la` is a buffer of
+// lds_elems<N>() slots that no other thread group uses; the caller must
 // not write it again before every thread has passed a barrier that follows
 // this call (it holds one exchange between a barrier and the gathers after
 // it).  The first transpose goes through the wavefront's own 512 slots of
 // `la` (a wavefront's LDS operations complete in order, and every other
 // wavefront's reads of `la` from the previous call precede the caller's
 // barrier before this one), with no workgroup barrier.
-template <typename T, int SIGN>
-__device__ __forceinline__ void fft4096_xw(C2<T> (&x)[8], C2<T>* __restrict__ la, const C2<T>* __restrict__ w,
-                                           int t)
+template <typename T, int N, int SIGN>
+__device__ __forceinline__ void fft_xw(C2<T> (&x)[8], C2<T>* __restrict__ la, const C2<T>* __restrict__ w, int t)
 {
+    constexpr int R2 = N / 512, B2 = 8 / R2;
     xw_pass<T, 1, SIGN>(x, w);
     {
         // in the wavefront's own block of `la`, the slots its workgroup
-        // exchange below writes (xw_slot keeps a block in place): register b
+        // exchange below writes: register b
         // of lane l at 64 b + (l ^ b); lane (lh, ll) reads register a at
         // 64 ll + ((8 lh + a) ^ ll) -- for 16 consecutive lanes 8 (lh mod 2)
         // + (a ^ ll) mod 16 are distinct, so no two share a bank
@@ -1006,17 +1036,30 @@ __device__ __forceinline__ void fft4096_xw(C2<T> (&x)[8], C2<T>* __restrict__ la
     xw_pass<T, 8, SIGN>(x, w);
     xw_transpose_hi(x);
     xw_pass<T, 64, SIGN>(x, w);
-    const int wv = t >> 6, l = t & 63;
+    {
+        // (the staging's swizzle here too: without it, base plus constant, the
+        // 4096-point kernel measured 0.7 % slower)
+        const int own = 512 * (t >> 6) + (t & 63);
 #pragma unroll
-    for (int r = 0; r < 8; ++r) la[xw_slot(512 * wv + 64 * r + l)] = x[r];
-    lds_barrier();
+        for (int r = 0; r < 8; ++r) la[xw_slot<N>(own + 64 * r)] = x[r];
+        lds_barrier();
 #pragma unroll
-    for (int r = 0; r < 8; ++r) x[r] = la[xw_slot(512 * r + 64 * wv + l)];
-    xw_pass<T, 512, SIGN>(x, w);
+        for (int b = 0; b < B2; ++b)
+#pragma unroll
+            for (int i = 0; i < R2; ++i) x[b * R2 + i] = la[xw_slot<N>(xw_out0<N>(t) + 64 * b + 512 * i)];
+    }
+    constexpr int LE = lf_entries(R2), OFF = tw_offset<N, 8, 8, TW_LFW>(512);
+#pragma unroll
+    for (int b = 0; b < B2; ++b) {
+        C2<T> L[LE];
+#pragma unroll
+        for (int e = 0; e < LE; ++e) L[e] = lf_sign<SIGN>(w[OFF + b * LE + e]);
+        lf_dft<R2, SIGN>(x + b * R2, L);
+    }
 }
 
 // Two 4096-point transforms (x and y, the same layout, direction and
-// twiddles) in fft4096_xw's form: both first transposes, one after the
+// twiddles) in fft_xw's form: both first transposes, one after the
 // other, in the wavefront's own block of `la`; both second transposes in
 // registers; the workgroup exchange of x through `la` and, after its
 // barrier, that of y through `lb` (the caller's staging buffer: every
@@ -1053,15 +1096,15 @@ __device__ __forceinline__ void fft4096_xw2(C2<T> (&x)[8], C2<T> (&y)[8], C2<T>*
     xw_pass<T, 64, SIGN, TWMODE>(y, w, ltw, t);
     const int wv = t >> 6, l = t & 63;
 #pragma unroll
-    for (int r = 0; r < 8; ++r) la[xw_slot(512 * wv + 64 * r + l)] = x[r];
+    for (int r = 0; r < 8; ++r) la[xw_slot<4096>(512 * wv + 64 * r + l)] = x[r];
     lds_barrier();
 #pragma unroll
-    for (int r = 0; r < 8; ++r) x[r] = la[xw_slot(512 * r + 64 * wv + l)];
+    for (int r = 0; r < 8; ++r) x[r] = la[xw_slot<4096>(512 * r + 64 * wv + l)];
 #pragma unroll
-    for (int r = 0; r < 8; ++r) lb[xw_slot(512 * wv + 64 * r + l)] = y[r];
+    for (int r = 0; r < 8; ++r) lb[xw_slot<4096>(512 * wv + 64 * r + l)] = y[r];
     lds_barrier();
 #pragma unroll
-    for (int r = 0; r < 8; ++r) y[r] = lb[xw_slot(512 * r + 64 * wv + l)];
+    for (int r = 0; r < 8; ++r) y[r] = lb[xw_slot<4096>(512 * r + 64 * wv + l)];
     xw_pass<T, 512, SIGN, TWMODE>(x, w, ltw, t);
     xw_pass<T, 512, SIGN, TWMODE>(y, w, ltw, t);
 }
