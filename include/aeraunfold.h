@@ -354,7 +354,10 @@ au_status au_pattern_response_quantized(const au_table* table, const au_event* e
  * atomic work counter, AU_PLAN_XCD to place all work units of one event on
  * one of the 8 XCDs (8 unit lists balanced by work; workgroup b takes units
  * from list b mod 8, then steals) so that the event's spectrum rows and its
- * directions' coefficient rows are fetched into one XCD's L2 only.
+ * directions' coefficient rows are fetched into one XCD's L2 only.  In FP64 the
+ * work is cut into equal shares, one per resident workgroup, when the plan is
+ * created or tuned; AU_PLAN_PERSISTENT then changes nothing, and AU_PLAN_XCD
+ * cuts the list into eighths, one per XCD.
  * With AU_PLAN_FUSED, trace-length classes (FP32, 2048 or 4096 samples,
  * bands of at most N/4 bins) whose events all have at most 64 directions
  * run fused (section 4's

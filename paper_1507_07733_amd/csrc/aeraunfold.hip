@@ -666,10 +666,17 @@ __global__ __launch_bounds__(kBlock) void k_coef(const C2<Tt>* __restrict__ node
 //   3. inverse FFT; thread t ends with z[t + (N/E) i], whose real and
 //      imaginary parts are E_theta and E_phi -- stored with non-temporal,
 //      coalesced writes.
-// With `counter` non-null the grid is persistent and blocks take units from
-// the atomic counter until the list is exhausted (every block leaves through
-// the same check); without, block b takes units b, b + grid, ...  Either way
-// the per-thread twiddles are loaded once per block.
+// Units: with `share` (FP64 plans) block b takes units [share[b], share[b + 1]),
+// which plan_shares cuts to equal work.  With `counter` (FP32, persistent grid)
+// blocks take units from the atomic counter until the list is exhausted (every
+// block leaves through the same check).  Without either, block b takes units b,
+// b + grid, ...  In each case the per-thread twiddles are loaded once per block.
+// Why the precisions differ: the wait for a fetched unit is a wait for every
+// store of the unit before it.  FP64 is bound inside the compute unit and pays
+// for it (32 events x 64 directions of 1024 to 4096 samples: 1238 us a pass with
+// the counter, 1184 with shares); FP32 is bound by the stores to HBM, which the
+// XCDs do not finish at one rate, and gains more from the counter's balance (40
+// events x 256 directions: 3250 us against 3322 with shares).
 // Lane -> FFT thread index.  With PAIR, every wavefront plays FFT threads t
 // (lanes 0-31) and TT - t (lanes 32-63, the partner of lane L is lane L ^ 32),
 // so the mirror bin N - k of any bin k a lane holds lives in the partner
@@ -764,7 +771,8 @@ __attribute__((amdgpu_waves_per_eu(unfold_min_waves<T, E, TWMODE, PAIR, PP>())))
                                                    T* __restrict__ efield,
                                                    const C2<T>* __restrict__ tw,
                                                    unsigned int* __restrict__ counter,
-                                                   const int* __restrict__ xcd_off)
+                                                   const int* __restrict__ xcd_off,
+                                                   const int* __restrict__ share)
 {
     constexpr int TT = N / E;
     constexpr int G = unfold_groups<T, N, E, TWMODE, PP>();
@@ -813,12 +821,23 @@ __attribute__((amdgpu_waves_per_eu(unfold_min_waves<T, E, TWMODE, PAIR, PP>())))
     // 8 XCDs, so block b runs on XCD b mod 8 and takes its units from that
     // list (persistent: from that list's counter, then from the other lists
     // once it is empty), and those rows are fetched into one XCD's L2 only.
-    if (threadIdx.x == 0) sh_list = blockIdx.x & 7;
+    if (sizeof(T) == 4 && threadIdx.x == 0) sh_list = blockIdx.x & 7;
     // XW: the band whose out-of-band slots of the staging buffer hold zeros
     unsigned zb_klo = ~0u, zb_nb = ~0u;
+    // FP64: units [u0, u1) in steps
+    unsigned u0 = blockIdx.x, u1 = (unsigned)n_units, u_step = gridDim.x;
+    if (sizeof(T) == 8 && share != nullptr) {
+        u0 = share[blockIdx.x];
+        u1 = share[blockIdx.x + 1];
+        u_step = 1;
+    }
     for (int iter = 0;; ++iter) {
         int u;
-        if (counter != nullptr) {
+        if (sizeof(T) == 8) {
+            if (u0 >= u1) break;
+            u = (int)u0;
+            u0 += u_step;
+        } else if (counter != nullptr) {
             if (threadIdx.x == 0) {
                 int got = n_units;
                 if (xcd_off != nullptr) {
@@ -853,7 +872,7 @@ __attribute__((amdgpu_waves_per_eu(unfold_min_waves<T, E, TWMODE, PAIR, PP>())))
                 u = v < n_units ? (int)v : n_units;
             }
         }
-        if (u >= n_units) break;
+        if (sizeof(T) == 4 && u >= n_units) break;
         int e = 0, d, s0, s1;
         if (units != nullptr) {
             const int4 wu = units[u];
@@ -1041,8 +1060,14 @@ __attribute__((amdgpu_waves_per_eu(unfold_min_waves<T, E, TWMODE, PAIR, PP>())))
             // Prefetch the next station's bins before this station's stores:
             // vector-memory completions are counted in issue order, so loads
             // issued after the stores would wait for every store to land.
-            // Branch-free, clamped to a valid station and bin.
+            // Branch-free, clamped to a valid station and bin.  In FP64 the
+            // scheduler is kept from moving stores ahead of these loads: with
+            // the first two stores in front, the next station's loads wait
+            // for them (scan of 124 stations x 4096 samples x 2048 directions
+            // 3543 us, so 3427; 61 x 4096 x 64 81.5, so 77.2; FP32 measures
+            // the same either way).
             if constexpr (PF > 0) prefetch_bins(Md, X + ev.x_off, min(s + G, s1 - 1), nb, tw, t);
+            if constexpr (sizeof(T) == 8) __builtin_amdgcn_sched_barrier(0);
             if constexpr (G == 1) {
                 // one group per block: its station is always active and the
                 // trace base uniform
@@ -2412,7 +2437,7 @@ static hipError_t launch_unfold_nv(hipStream_t st, const EvDesc& ev0, const EvDe
                                    const int4* units, int n_units, int spw, const XBin<T>* X,
                                    const MBin<T>* M, T* efield, const C2<T>* tw,
                                    unsigned int* counter, int persistent_blocks, const int* xcd_off,
-                                   int xcd_max_list)
+                                   int xcd_max_list, const int* share)
 {
     if constexpr (!variant_built(N, V, (int)sizeof(T))) {
         return hipErrorInvalidValue;
@@ -2420,7 +2445,9 @@ static hipError_t launch_unfold_nv(hipStream_t st, const EvDesc& ev0, const EvDe
         using S = UShape<T, N, V>;
         if (n_units <= 0) return hipSuccess;
         int grid;
-        if (counter != nullptr) {
+        if (share != nullptr) {
+            grid = persistent_blocks;
+        } else if (counter != nullptr) {
             hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, st, counter, 8);
             grid = std::min(n_units, persistent_blocks);
         } else {
@@ -2432,7 +2459,7 @@ static hipError_t launch_unfold_nv(hipStream_t st, const EvDesc& ev0, const EvDe
             grid = xcd_off != nullptr ? 8 * std::max(1, std::min(xcd_max_list, cap / 8)) : std::min(n_units, cap);
         }
         hipLaunchKernelGGL((k_unfold<T, N, S::E, S::RMAX, S::TWMODE, S::WAVE, S::PAIR, S::PP>), dim3(grid), dim3(S::BLOCK), S::LDS, st,
-                           ev0, evs, units, n_units, spw, X, M, efield, tw, counter, xcd_off);
+                           ev0, evs, units, n_units, spw, X, M, efield, tw, counter, xcd_off, share);
         return hipGetLastError();
     }
 }
@@ -2442,11 +2469,11 @@ static hipError_t launch_unfold_n(int v, hipStream_t st, const EvDesc& ev0, cons
                                   const int4* units, int n_units, int spw, const XBin<T>* X,
                                   const MBin<T>* M, T* efield, const C2<T>* tw,
                                   unsigned int* counter, int persistent_blocks, const int* xcd_off,
-                                  int xcd_max_list)
+                                  int xcd_max_list, const int* share)
 {
     switch (v) {
 #define V_(VV) \
-    case VV: return launch_unfold_nv<T, N, VV>(st, ev0, evs, units, n_units, spw, X, M, efield, tw, counter, persistent_blocks, xcd_off, xcd_max_list);
+    case VV: return launch_unfold_nv<T, N, VV>(st, ev0, evs, units, n_units, spw, X, M, efield, tw, counter, persistent_blocks, xcd_off, xcd_max_list, share);
         V_(0) V_(1) V_(2) V_(3) V_(4) V_(5) V_(6) V_(7) V_(8) V_(9) V_(10) V_(11) V_(12) V_(13) V_(14) V_(15)
         V_(16) V_(17)
 #undef V_
@@ -2487,13 +2514,14 @@ template <typename T>
 static hipError_t launch_unfold(int n, int v, hipStream_t st, const EvDesc& ev0, const EvDesc* evs,
                                 const int4* units, int n_units, int spw, const XBin<T>* X,
                                 const MBin<T>* M, T* efield, const C2<T>* tw, unsigned int* counter,
-                                int persistent_blocks, const int* xcd_off = nullptr, int xcd_max_list = 0)
+                                int persistent_blocks, const int* xcd_off = nullptr, int xcd_max_list = 0,
+                                const int* share = nullptr)
 {
     switch (n) {
 #define X_(NN)                                                                                  \
     case NN:                                                                                    \
         return launch_unfold_n<T, NN>(v, st, ev0, evs, units, n_units, spw, X, M, efield, tw,   \
-                                      counter, persistent_blocks, xcd_off, xcd_max_list);
+                                      counter, persistent_blocks, xcd_off, xcd_max_list, share);
         AU_FOR_EACH_N(X_)
 #undef X_
     }
@@ -2534,6 +2562,30 @@ static int persistent_blocks_for(int n, int v, int device)
 #undef X_
     }
     return cus * std::max(per_cu, 1);
+}
+
+// Stations that a workgroup of an unfold variant takes side by side.
+template <typename T, int N, int V>
+constexpr int unfold_stations_nv()
+{
+    if constexpr (variant_built(N, V, (int)sizeof(T))) return UShape<T, N, V>::G;
+    return 1;
+}
+
+template <typename T>
+static int unfold_stations(int n, int v)
+{
+    switch (n * kNumVariants + v) {
+#define V_(NN, VV) \
+    case NN * kNumVariants + VV: return unfold_stations_nv<T, NN, VV>();
+#define X_(NN)                                                                                              \
+    V_(NN, 0) V_(NN, 1) V_(NN, 2) V_(NN, 3) V_(NN, 4) V_(NN, 5) V_(NN, 6) V_(NN, 7) V_(NN, 8) V_(NN, 9)     \
+    V_(NN, 10) V_(NN, 11) V_(NN, 12) V_(NN, 13) V_(NN, 14) V_(NN, 15) V_(NN, 16) V_(NN, 17)
+        AU_FOR_EACH_N(X_)
+#undef X_
+#undef V_
+    }
+    return 1;
 }
 
 // ---------------------------------------------------------------------------
@@ -3246,6 +3298,9 @@ struct ClassPlan {
     int xcd_max_list = 0;
     int max_nb = 0;  // largest band of the class's events (bins)
     bool fused = false;  // spectrum and unfold in k_unfold_fused (units: event, station range)
+    // FP64: the unfold's units in equal shares, one per workgroup (plan_shares)
+    std::vector<int2> ev_sd;  // stations and directions of each event
+    int* d_share = nullptr;
 };
 
 struct au_plan {
@@ -3328,7 +3383,8 @@ static au_status enqueue_class_t(const au_table* tb, int tin, int64_t fs, double
     }
     if (stage_events) HIP_TRY(hipEventRecord(stage_events[1], st));
     e = launch_unfold<T>(c.N, c.variant, st, ev0, c.d_evs, c.d_uunits, c.n_uunits, kStationsPerUnit, X, M,
-                         (T*)efield, tw, c.d_counter, c.persistent_blocks, c.d_xcd_off, c.xcd_max_list);
+                         (T*)efield, tw, c.d_counter, c.persistent_blocks, c.d_xcd_off, c.xcd_max_list,
+                         c.d_share);
     if (e != hipSuccess) return fail(AU_EDEVICE, std::string("k_unfold: ") + hipGetErrorString(e));
     if (stage_events) HIP_TRY(hipEventRecord(stage_events[2], st));
     return AU_OK;
@@ -3370,6 +3426,7 @@ static au_status plan_enqueue(au_plan* pl, const void* d_volt, void* d_efield, h
         c.d_uunits = cp.d_uunits;
         c.n_uunits = cp.n_uunits;
         c.d_counter = (pers || cp.fused) ? cp.d_counter : nullptr;
+        c.d_share = cp.d_share;
         c.fused = cp.fused;
         c.persistent_blocks = cp.persistent_blocks;
         c.d_xcd_off = cp.d_xcd_off;
@@ -3390,6 +3447,69 @@ static au_status plan_enqueue(au_plan* pl, const void* d_volt, void* d_efield, h
         ++pl->timed_runs;
     }
     return AU_OK;
+}
+
+// Most shares of a class: wavefronts that the device can hold.
+constexpr int kMaxShares = 256 * 32;
+// Stations of a share that lie side by side in the output (8 and 64 measured the same).
+constexpr int kPieceStations = 32;
+
+// Cuts an FP64 class's (event, direction) rows into the units of equal shares, one
+// per workgroup that the device holds of the class's unfold shape, and copies units
+// and boundaries to the device (synchronous; nothing of the class may be running).
+// Work is counted in rounds of the stations a workgroup takes side by side.  A
+// share is one piece of each of `turns` equal parts of the list, so that the
+// workgroups write one region together (one piece per share: 3 % slower).  With
+// xcd the list is cut into eighths first, for the workgroups b of equal b mod 8:
+// these run on one XCD, whose L2 then fetches an event's spectrum rows, and each
+// direction's coefficient row, alone.
+static hipError_t plan_shares(ClassPlan& c, bool xcd)
+{
+    const int G = unfold_stations<double>(c.N, c.variant);
+    int64_t total = 0;
+    for (const int2& e : c.ev_sd) total += (int64_t)((e.x + G - 1) / G) * e.y;
+    // a multiple of 8; an empty share does no harm
+    const int shares =
+        (int)std::min<int64_t>(std::min(c.persistent_blocks, kMaxShares) / 8 * 8, (total + 7) / 8 * 8);
+    const int lists = xcd ? 8 : 1, per_list = shares / lists;
+    const int64_t turns = std::max<int64_t>(1, total * G / ((int64_t)shares * kPieceStations));
+    const int64_t pieces = shares * turns;
+    // the list in order, cut at the pieces' ends
+    auto piece_end = [&](int64_t p) { return (int64_t)((__int128)total * p / pieces); };
+    std::vector<int4> list;
+    std::vector<int> first(1, 0);  // of each piece in `list`
+    list.reserve((size_t)(c.n_cunits + pieces));
+    first.reserve((size_t)pieces + 1);
+    int64_t at = 0;
+    for (int e = 0; e < (int)c.ev_sd.size(); ++e) {
+        const int S = c.ev_sd[e].x;
+        for (int d = 0; d < c.ev_sd[e].y; ++d)
+            for (int s0 = 0; s0 < S;) {
+                while (piece_end((int64_t)first.size()) <= at) first.push_back((int)list.size());
+                const int s1 = (int)std::min<int64_t>(S, s0 + (piece_end((int64_t)first.size()) - at) * G);
+                list.push_back(int4{e, d, s0, s1});
+                at += (s1 - s0 + G - 1) / G;
+                s0 = s1;
+            }
+    }
+    first.resize((size_t)pieces + 1, (int)list.size());
+    // workgroup by workgroup
+    std::vector<int4> units;
+    std::vector<int> share(1, 0);
+    units.reserve(list.size());
+    for (int b = 0; b < shares; ++b) {
+        const int64_t l = b % lists, i = b / lists;
+        for (int64_t k = 0; k < turns; ++k) {
+            const int64_t p = (l * turns + k) * per_list + i;
+            units.insert(units.end(), list.begin() + first[p], list.begin() + first[p + 1]);
+        }
+        share.push_back((int)units.size());
+    }
+    c.n_uunits = (int)units.size();
+    c.persistent_blocks = shares;
+    hipError_t e = hipMemcpy(c.d_uunits, units.data(), units.size() * sizeof(int4), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(c.d_share, share.data(), share.size() * sizeof(int), hipMemcpyHostToDevice);
+    return e;
 }
 
 extern "C" au_status au_plan_free(au_plan* pl)
@@ -3477,12 +3597,15 @@ extern "C" au_status au_plan_create(const au_table* tb, const au_batch* b, au_pl
         std::vector<int4> uu;
         std::vector<int> xcd_off;
         int xcd_max = 0;
+        bool shared = false;   // FP64 unfold: units cut by plan_shares, at most units_cap
+        size_t units_cap = 0;
     };
     std::vector<HostClass> hc;
     for (int n : ns) {
         HostClass c;
         c.N = n;
         c.fused = class_fused(n);
+        c.shared = f64 && !c.fused;
         for (int e = 0; e < E; ++e) {
             if (descs[e].N != n) continue;
             const int ci = (int)c.evs.size();
@@ -3497,6 +3620,7 @@ extern "C" au_status au_plan_create(const au_table* tb, const au_batch* b, au_pl
             for (int st = 0; st < descs[e].S; ++st) c.su.push_back(int2{ci, st});
             for (int d = 0; d < descs[e].D; ++d) {
                 c.cu.push_back(int2{ci, d});
+                if (c.shared) continue;
                 // events with many directions have units to spare: chunks of
                 // twice the stations halve the per-unit start (work fetch and
                 // the first station's loads) -- measured +1.5 % on 256
@@ -3506,7 +3630,7 @@ extern "C" au_status au_plan_create(const au_table* tb, const au_batch* b, au_pl
                     c.uu.push_back(int4{ci, d, s0, std::min(descs[e].S, s0 + cs)});
             }
         }
-        if (b->flags & AU_PLAN_XCD) {
+        if ((b->flags & AU_PLAN_XCD) && !c.shared) {
             // all units of one event (its directions' station chunks) go to one
             // of 8 lists, the list with the least work so far (work =
             // stations): the event's spectrum rows and each direction's
@@ -3536,7 +3660,13 @@ extern "C" au_status au_plan_create(const au_table* tb, const au_batch* b, au_pl
             std::stable_sort(c.uu.begin(), c.uu.end(),
                              [](const int4& a, const int4& bb) { return (a.w - a.z) > (bb.w - bb.z); });
         }
-        if (c.uu.size() > 0x7fffffffu || c.cu.size() > 0x7fffffffu || c.su.size() > 0x7fffffffu)
+        c.units_cap = c.uu.size();
+        if (c.shared) {  // rows and pieces (with at most 255 stations of padding in a row)
+            size_t stations = 0;
+            for (const EvDesc& d : c.evs) stations += (size_t)(d.S + 255) * d.D;
+            c.units_cap = c.cu.size() + kMaxShares + stations / kPieceStations;
+        }
+        if (c.units_cap > 0x7fffffffu || c.cu.size() > 0x7fffffffu || c.su.size() > 0x7fffffffu)
             return fail(AU_EINVAL, "too many work units in one trace-length class");
         hc.push_back(std::move(c));
     }
@@ -3551,13 +3681,14 @@ extern "C" au_status au_plan_create(const au_table* tb, const au_batch* b, au_pl
     const size_t o_m = take((size_t)m_total * mb);
     const size_t o_dirs = take((size_t)dir_total * 2 * sizeof(double));
     struct Offs {
-        size_t evs, su, cu, uu, ctr, xoff;
+        size_t evs, su, cu, uu, ctr, xoff, share;
     };
     std::vector<Offs> co;
     for (auto& c : hc)
         co.push_back(Offs{take(c.evs.size() * sizeof(EvDesc)), take(c.su.size() * sizeof(int2)),
-                          take(c.cu.size() * sizeof(int2)), take(c.uu.size() * sizeof(int4)),
-                          take(8 * sizeof(unsigned int)), take(9 * sizeof(int))});
+                          take(c.cu.size() * sizeof(int2)), take(c.units_cap * sizeof(int4)),
+                          take(8 * sizeof(unsigned int)), take(9 * sizeof(int)),
+                          take(c.shared ? (kMaxShares + 1) * sizeof(int) : 0)});
     au_plan* pl = new au_plan();
     pl->tb = tb;
     pl->device = dev;
@@ -3610,10 +3741,16 @@ extern "C" au_status au_plan_create(const au_table* tb, const au_batch* b, au_pl
         PLAN_TRY(hipMemcpy(c.d_evs, hc[i].evs.data(), hc[i].evs.size() * sizeof(EvDesc), hipMemcpyHostToDevice));
         PLAN_TRY(hipMemcpy(c.d_sunits, hc[i].su.data(), hc[i].su.size() * sizeof(int2), hipMemcpyHostToDevice));
         PLAN_TRY(hipMemcpy(c.d_cunits, hc[i].cu.data(), hc[i].cu.size() * sizeof(int2), hipMemcpyHostToDevice));
-        PLAN_TRY(hipMemcpy(c.d_uunits, hc[i].uu.data(), hc[i].uu.size() * sizeof(int4), hipMemcpyHostToDevice));
+        if (!hc[i].shared)
+            PLAN_TRY(hipMemcpy(c.d_uunits, hc[i].uu.data(), hc[i].uu.size() * sizeof(int4), hipMemcpyHostToDevice));
         c.variant = unfold_variant(b->prec, c.N);
         c.persistent_blocks = f64 ? persistent_blocks_for<double>(c.N, c.variant, dev)
                                   : persistent_blocks_for<float>(c.N, c.variant, dev);
+        if (hc[i].shared) {
+            c.d_share = (int*)(base + co[i].share);
+            for (const EvDesc& d : hc[i].evs) c.ev_sd.push_back(int2{d.S, d.D});
+            PLAN_TRY(plan_shares(c, (b->flags & AU_PLAN_XCD) != 0));
+        }
         pl->classes.push_back(c);
     }
     if (pl->flags & AU_PLAN_GRAPH) PLAN_TRY(hipStreamCreateWithFlags(&pl->cap_stream, hipStreamNonBlocking));
@@ -3716,6 +3853,16 @@ extern "C" au_status au_plan_autotune(au_plan* pl, const void* d_volt, void* d_e
     HIP_TRY(hipGetDevice(&dev));
     if (dev != pl->device) return fail(AU_EINVAL, "plan lives on another device");
     hipStream_t st = (hipStream_t)stream;
+    // another unfold shape, and its shares of the units (the stream is idle: each
+    // timed run has been waited for)
+    auto set_variant = [&](ClassPlan& cp, int v) {
+        cp.variant = v;
+        cp.persistent_blocks = au::persistent_blocks(pl->prec, cp.N, v, pl->device);
+        if (cp.d_share == nullptr) return AU_OK;
+        const hipError_t e = plan_shares(cp, (pl->flags & AU_PLAN_XCD) != 0);
+        return e == hipSuccess ? AU_OK : fail(AU_EDEVICE, std::string("work shares: ") + hipGetErrorString(e));
+    };
+    HIP_TRY(hipStreamSynchronize(st));
     const bool was_timing = pl->timing;
     const std::vector<double> saved_ms = pl->stage_ms;
     const uint64_t saved_runs = pl->timed_runs;
@@ -3738,8 +3885,8 @@ extern "C" au_status au_plan_autotune(au_plan* pl, const void* d_volt, void* d_e
         for (int v = 0; v < kNumVariants && rc == AU_OK; ++v) {
             if (ms) ms[i * kNumVariants + v] = -1.0;
             if (!variant_built(cp.N, v, tsize)) continue;
-            cp.variant = v;
-            cp.persistent_blocks = au::persistent_blocks(pl->prec, cp.N, v, pl->device);
+            rc = set_variant(cp, v);
+            if (rc != AU_OK) break;
             pl->timing = false;
             rc = plan_enqueue(pl, d_volt, d_efield, st, nullptr);  // warm-up
             pl->timing = true;
@@ -3754,8 +3901,8 @@ extern "C" au_status au_plan_autotune(au_plan* pl, const void* d_volt, void* d_e
                 best_v = v;
             }
         }
-        cp.variant = best_v;
-        cp.persistent_blocks = au::persistent_blocks(pl->prec, cp.N, best_v, pl->device);
+        const au_status rs = set_variant(cp, best_v);
+        if (rc == AU_OK) rc = rs;
         if (best) best[i] = best_v;
     }
     pl->timing = was_timing;

@@ -58,6 +58,7 @@ struct ClassLaunch {
     int n_uunits = 0;
     unsigned int* d_counter = nullptr;  // non-null: persistent unfold grid (8 counters)
     int persistent_blocks = 0;
+    const int* d_share = nullptr;       // non-null: boundaries of the workgroups' shares of the units
     const int* d_xcd_off = nullptr;     // non-null: 8 per-XCD unit lists (9 boundaries)
     int xcd_max_list = 0;               // longest of the 8 lists
     int max_nb = 1 << 30;               // largest band of the events, in bins (default: unknown)
