@@ -348,12 +348,13 @@ __device__ __forceinline__ void wave_first_max(double pw, unsigned n_minus, unsi
 // Against k_spectrum, double precision, 124 stations x 4096 samples: 13.9 ->
 // 11.5 us; with k_volt_timing, 96 events of 3 to 124 stations x 4096 float
 // samples: 108 -> 70 us.
+// The work of workgroup bx of `blocks`.
 template <typename Tin, typename T, int N, bool TIMING>
-__global__ __launch_bounds__(N / 8) void k_spectrum_stream(const Tin* __restrict__ volt, EvDesc ev0,
-                                                           const EvDesc* __restrict__ evs,
-                                                           const int2* __restrict__ units, int n_units,
-                                                           XBin<T>* __restrict__ X,
-                                                           const C2<T>* __restrict__ tw, int* __restrict__ t0)
+__device__ __forceinline__ void spectrum_stream_block(int bx, int blocks, const Tin* __restrict__ volt,
+                                                      const EvDesc& ev0, const EvDesc* __restrict__ evs,
+                                                      const int2* __restrict__ units, int n_units,
+                                                      XBin<T>* __restrict__ X, const C2<T>* __restrict__ tw,
+                                                      int* __restrict__ t0)
 {
     constexpr int E = 8, RMAX = 8, TT = N / E, NW = TT / 64;
     static_assert(kSpecStreamBins * TT <= N, "gathered bins stay inside the transform");
@@ -391,7 +392,7 @@ __global__ __launch_bounds__(N / 8) void k_spectrum_stream(const Tin* __restrict
         const int k_lo = evs ? evs[e].k_lo : ev0.k_lo;
         return Row{volt + volt_off + (int64_t)s * 2 * N, X + x_off + (int64_t)s * nb, nb, k_lo};
     };
-    int u = blockIdx.x;
+    int u = bx;
     Row row = locate(u);
     Tin a[E], b[E];
 #pragma unroll
@@ -425,7 +426,7 @@ __global__ __launch_bounds__(N / 8) void k_spectrum_stream(const Tin* __restrict
                 first[2][t >> 6] = at;
             }
         }
-        const int un = u + (int)gridDim.x;
+        const int un = u + blocks;
         Row next = row;
         if (un < n_units) {
             next = locate(un);
@@ -469,6 +470,16 @@ __global__ __launch_bounds__(N / 8) void k_spectrum_stream(const Tin* __restrict
         u = un;
         row = next;
     }
+}
+
+template <typename Tin, typename T, int N, bool TIMING>
+__global__ __launch_bounds__(N / 8) void k_spectrum_stream(const Tin* __restrict__ volt, EvDesc ev0,
+                                                           const EvDesc* __restrict__ evs,
+                                                           const int2* __restrict__ units, int n_units,
+                                                           XBin<T>* __restrict__ X,
+                                                           const C2<T>* __restrict__ tw, int* __restrict__ t0)
+{
+    spectrum_stream_block<Tin, T, N, TIMING>(blockIdx.x, gridDim.x, volt, ev0, evs, units, n_units, X, tw, t0);
 }
 
 // Coefficients of every in-band bin of one (event, direction) per block.
@@ -526,9 +537,10 @@ __device__ __forceinline__ MBin<T> coef_from_h(const C2<T> (&h)[4], int n, T inv
     return m;
 }
 
-// The work of workgroup bx of k_coef.  dirs and skip may be written earlier
-// in the same kernel (by another thread of the workgroup, before a barrier).
-template <typename Tt, typename T, bool RESP>
+// The work of workgroup bx of k_coef, of at most BLOCK threads.  dirs and skip
+// may be written earlier in the same kernel (by another thread of the workgroup,
+// before a barrier).
+template <typename Tt, typename T, bool RESP, int BLOCK = kBlock>
 __device__ __forceinline__ void coef_block(int bx, const C2<Tt>* __restrict__ nodes, const GridDev& gd,
                                            const EvDesc& ev0, const EvDesc* __restrict__ evs,
                                            const int2* __restrict__ units, const double* dirs, double zen1,
@@ -582,7 +594,7 @@ __device__ __forceinline__ void coef_block(int bx, const C2<Tt>* __restrict__ no
         n_nodes = f_hi - f_lo + 2;
     }
     constexpr int kRecWords = (int)(sizeof(MBin<T>) / 16);
-    __shared__ uint4 stage[kBlock * kRecWords];
+    __shared__ uint4 stage[BLOCK * kRecWords];
     const bool one_window = n_nodes <= kMaxSliceNodes;  // uniform
     for (int w0 = 0; w0 < n_nodes - 1; w0 += kMaxSliceNodes - 1) {
         const int wn = min(kMaxSliceNodes, n_nodes - w0);  // uniform over the workgroup
@@ -654,6 +666,26 @@ __global__ __launch_bounds__(kBlock) void k_coef(const C2<Tt>* __restrict__ node
 {
     coef_block<Tt, T, RESP>(blockIdx.x, nodes, gd, ev0, evs, units, dirs, zen1, az1, fs, fallback_rel, singular_rel,
                             M, counts, wq, skip, skip_stride);
+}
+
+// A scan's spectra and coefficients, which depend on nothing of each other, in
+// one launch: the first spec_blocks workgroups are k_spectrum_stream's, the
+// others one direction's k_coef each.
+template <typename Tin, typename Tt, typename T, int N>
+__global__ __launch_bounds__(N / 8) void k_spectrum_coef(const Tin* __restrict__ volt, EvDesc ev0, int spec_blocks,
+                                                         XBin<T>* __restrict__ X, const C2<T>* __restrict__ tw,
+                                                         const C2<Tt>* __restrict__ nodes, GridDev gd,
+                                                         const double* __restrict__ dirs, double zen1, double az1,
+                                                         int64_t fs, double fallback_rel, double singular_rel,
+                                                         MBin<T>* __restrict__ M,
+                                                         unsigned long long* __restrict__ counts)
+{
+    if ((int)blockIdx.x < spec_blocks)
+        spectrum_stream_block<Tin, T, N, false>(blockIdx.x, spec_blocks, volt, ev0, nullptr, nullptr, ev0.S, X, tw,
+                                                nullptr);
+    else
+        coef_block<Tt, T, false, N / 8>(blockIdx.x - spec_blocks, nodes, gd, ev0, nullptr, nullptr, dirs, zen1, az1, fs,
+                                        fallback_rel, singular_rel, M, counts, 0.0, nullptr, 0);
 }
 
 // E-field traces of one (event, direction, station range) per block; each
@@ -2882,6 +2914,79 @@ static void launch_coef(hipStream_t st, const au_table* tb, const EvDesc& ev0, c
                        M, counts, 0.0, skip, skip_stride);
 }
 
+// k_spectrum_coef at N samples; false where the spectra take another kernel.
+template <typename Tin, typename Tt, typename T, int N>
+static bool launch_spectrum_coef_n(hipStream_t st, const au_table* tb, const au_event* ev, const EvDesc& ev0,
+                                   const Tin* volt, const double* dirs, double zen, double az, XBin<T>* X, MBin<T>* M,
+                                   const C2<T>* tw, unsigned long long* counts)
+{
+    if constexpr (N < 512 || sizeof(Tt) < sizeof(T)) {  // (FP64 takes tables in double only)
+        return false;
+    } else {
+        const int blocks = spectrum_stream_blocks<Tin, T, N, false>();
+        if (ev0.nb > kSpecStreamBins * (N / 8) || blocks <= 0) return false;
+        const int spec = std::min(ev0.S, blocks);
+        hipLaunchKernelGGL((k_spectrum_coef<Tin, Tt, T, N>), dim3(spec + ev0.D), dim3(N / 8),
+                           (spectrum_stream_lds<T, N>()), st, volt, ev0, spec, X, tw, (const C2<Tt>*)tb->d_nodes, tb->g,
+                           dirs, zen, az, ev->fs_hz, ev->fallback_rel, ev->singular_rel, M, counts);
+        return true;
+    }
+}
+
+template <typename Tin, typename Tt, typename T>
+static bool launch_spectrum_coef_t(hipStream_t st, const au_table* tb, const au_event* ev, const EvDesc& ev0,
+                                   const void* volt, const double* dirs, double zen, double az, XBin<T>* X, MBin<T>* M,
+                                   const C2<T>* tw, unsigned long long* counts)
+{
+    switch (ev0.N) {
+#define X_(NN)                                                                                                        \
+    case NN:                                                                                                          \
+        return launch_spectrum_coef_n<Tin, Tt, T, NN>(st, tb, ev, ev0, (const Tin*)volt, dirs, zen, az, X, M, tw, counts);
+        AU_FOR_EACH_N(X_)
+#undef X_
+    }
+    return false;
+}
+
+// The spectra of one event's stations and the coefficients of its ev0.D
+// directions (dirs, or with null the one direction zen, az).  In one launch
+// while the directions' workgroups fit the device at once (256 of 4096 samples,
+// twice as many of half the length): a launch costs 4 to 5 us and neither half
+// fills the device.  Above, the coefficients are better off in k_coef's smaller
+// workgroups.  Scan, apart -> in one launch: FP32 61 stations x 2048 samples x 64
+// directions 29.5 -> 25.5 us, 61 x 4096 x 64 47.2 -> 40.8, 33 x 1024 x 256 34.9 ->
+// 31.8, 10 x 512 x 40 20.3 -> 18.3; FP64 20 x 4096 x 16 34.2 -> 26.4, 5 x 4096 x
+// 256 42.9 -> 43.1, 5 x 4096 x 512 65.0 -> 67.0.
+constexpr int64_t kSpecCoefWork = 256 * 4096;  // directions x samples
+template <typename T>
+static au_status spectrum_and_coef(hipStream_t st, const au_table* tb, const au_event* ev, const EvDesc& ev0,
+                                   const void* volt, const double* dirs, double zen, double az, XBin<T>* X, MBin<T>* M,
+                                   const C2<T>* tw, unsigned long long* counts)
+{
+    const bool tin64 = ev->trace_dtype == AU_F64, tab64 = tb->dtype == AU_F64;
+    bool done = false;
+    if ((int64_t)ev0.D * ev0.N <= kSpecCoefWork)
+        done = tin64 ? (tab64 ? launch_spectrum_coef_t<double, double, T>(st, tb, ev, ev0, volt, dirs, zen, az, X, M, tw, counts)
+                              : launch_spectrum_coef_t<double, float, T>(st, tb, ev, ev0, volt, dirs, zen, az, X, M, tw, counts))
+                     : (tab64 ? launch_spectrum_coef_t<float, double, T>(st, tb, ev, ev0, volt, dirs, zen, az, X, M, tw, counts)
+                              : launch_spectrum_coef_t<float, float, T>(st, tb, ev, ev0, volt, dirs, zen, az, X, M, tw, counts));
+    if (done) {
+        const hipError_t e = hipGetLastError();
+        return e == hipSuccess ? AU_OK : fail(AU_EDEVICE, std::string("k_spectrum_coef: ") + hipGetErrorString(e));
+    }
+    hipError_t e = tin64 ? launch_spectrum<double, T>(ev0.N, st, (const double*)volt, ev0, nullptr, nullptr, ev0.S, ev0.nb, X, tw)
+                         : launch_spectrum<float, T>(ev0.N, st, (const float*)volt, ev0, nullptr, nullptr, ev0.S, ev0.nb, X, tw);
+    if (e != hipSuccess) return fail(AU_EDEVICE, std::string("k_spectrum: ") + hipGetErrorString(e));
+    if (tab64)
+        launch_coef<double, T>(st, tb, ev0, nullptr, nullptr, ev0.D, dirs, zen, az, ev->fs_hz, ev->fallback_rel,
+                               ev->singular_rel, M, counts);
+    else
+        launch_coef<float, T>(st, tb, ev0, nullptr, nullptr, ev0.D, dirs, zen, az, ev->fs_hz, ev->fallback_rel,
+                              ev->singular_rel, M, counts);
+    e = hipGetLastError();
+    return e == hipSuccess ? AU_OK : fail(AU_EDEVICE, std::string("k_coef: ") + hipGetErrorString(e));
+}
+
 // Stations per work unit of a direction scan (one event, n_dir directions;
 // units (direction, station range) spread over a grid of up to `blocks`
 // that each loop over their share): from 16, halved while there are fewer
@@ -3006,22 +3111,10 @@ static au_status run_event(const au_table* tb, const au_event* ev, const EvParam
     ev0.nb = p.nb;
     const C2<T>* tw = twiddles<T>(tb->device);
     if (tw == nullptr) return fail(AU_EDEVICE, "twiddle tables missing on this device");
+    const au_status rc = spectrum_and_coef<T>(st, tb, ev, ev0, d_volt, h_dirs ? dirs : nullptr, zen, az, X, M, tw,
+                                              (unsigned long long*)d_counts);
+    if (rc != AU_OK) return rc;
     hipError_t e;
-    if (ev->trace_dtype == AU_F64)
-        e = launch_spectrum<double, T>(p.N, st, (const double*)d_volt, ev0, nullptr, nullptr, p.S, ev0.nb, X, tw);
-    else
-        e = launch_spectrum<float, T>(p.N, st, (const float*)d_volt, ev0, nullptr, nullptr, p.S, ev0.nb, X, tw);
-    if (e != hipSuccess) return fail(AU_EDEVICE, std::string("k_spectrum: ") + hipGetErrorString(e));
-    unsigned long long* cnt = (unsigned long long*)d_counts;
-    if (tb->dtype == AU_F64)
-        launch_coef<double, T>(st, tb, ev0, nullptr, nullptr, n_dir, h_dirs ? dirs : nullptr, zen,
-                               az, ev->fs_hz, ev->fallback_rel, ev->singular_rel, M,
-                               cnt);
-    else
-        launch_coef<float, T>(st, tb, ev0, nullptr, nullptr, n_dir, h_dirs ? dirs : nullptr, zen, az,
-                              ev->fs_hz, ev->fallback_rel, ev->singular_rel, M, cnt);
-    e = hipGetLastError();
-    if (e != hipSuccess) return fail(AU_EDEVICE, std::string("k_coef: ") + hipGetErrorString(e));
     const int spw = scan_stations_per_unit(p.S, n_dir, scan_blocks(ev->prec, p.N, variant, tb->device));
     const int chunks = (p.S + spw - 1) / spw;
     const int64_t n_units = (int64_t)n_dir * chunks;
@@ -4239,20 +4332,10 @@ static au_status run_envelope(const au_table* tb, const au_event* ev, const EvPa
     ev0.nb = p.nb;
     const C2<T>* tw = twiddles<T>(tb->device);
     if (tw == nullptr) return fail(AU_EDEVICE, "twiddle tables missing on this device");
+    const au_status rc = spectrum_and_coef<T>(st, tb, ev, ev0, d_volt, dirs, 0, 0, X, M, tw,
+                                              (unsigned long long*)d_counts);
+    if (rc != AU_OK) return rc;
     hipError_t e;
-    if (ev->trace_dtype == AU_F64)
-        e = launch_spectrum<double, T>(p.N, st, (const double*)d_volt, ev0, nullptr, nullptr, p.S, ev0.nb, X, tw);
-    else
-        e = launch_spectrum<float, T>(p.N, st, (const float*)d_volt, ev0, nullptr, nullptr, p.S, ev0.nb, X, tw);
-    if (e != hipSuccess) return fail(AU_EDEVICE, std::string("k_spectrum: ") + hipGetErrorString(e));
-    if (tb->dtype == AU_F64)
-        launch_coef<double, T>(st, tb, ev0, nullptr, nullptr, n_dir, dirs, 0, 0, ev->fs_hz, ev->fallback_rel,
-                               ev->singular_rel, M, (unsigned long long*)d_counts);
-    else
-        launch_coef<float, T>(st, tb, ev0, nullptr, nullptr, n_dir, dirs, 0, 0, ev->fs_hz, ev->fallback_rel,
-                              ev->singular_rel, M, (unsigned long long*)d_counts);
-    e = hipGetLastError();
-    if (e != hipSuccess) return fail(AU_EDEVICE, std::string("k_coef: ") + hipGetErrorString(e));
     const int spw = env_spw(p.S, n_dir);
     const int chunks = (p.S + spw - 1) / spw;
     const int64_t n_units = (int64_t)n_dir * chunks;
