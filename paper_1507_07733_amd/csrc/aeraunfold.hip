@@ -546,7 +546,7 @@ __device__ __forceinline__ void coef_block(int bx, const C2<Tt>* __restrict__ no
                                            const int2* __restrict__ units, const double* dirs, double zen1,
                                            double az1, int64_t fs, double fallback_rel, double singular_rel,
                                            MBin<T>* __restrict__ M, unsigned long long* __restrict__ counts,
-                                           double wq, const int* skip, int skip_stride)
+                                           double wq, const int* skip)
 {
     __shared__ unsigned int cnt[2];
     if (threadIdx.x < 2) cnt[threadIdx.x] = 0;
@@ -558,7 +558,7 @@ __device__ __forceinline__ void coef_block(int bx, const C2<Tt>* __restrict__ no
         d = w.y;
     }
     // a converged reconstruction loop: its envelope launch is skipped too
-    if (skip != nullptr && skip[(int64_t)e * skip_stride]) return;
+    if (skip != nullptr && *skip) return;
     const EvDesc ev = evs ? evs[e] : ev0;
     double zen = zen1, az = az1;
     if (dirs != nullptr) {
@@ -661,11 +661,10 @@ __global__ __launch_bounds__(kBlock) void k_coef(const C2<Tt>* __restrict__ node
                                                  const double* __restrict__ dirs, double zen1,
                                                  double az1, int64_t fs, double fallback_rel,
                                                  double singular_rel, MBin<T>* __restrict__ M,
-                                                 unsigned long long* __restrict__ counts, double wq,
-                                                 const int* __restrict__ skip = nullptr, int skip_stride = 0)
+                                                 unsigned long long* __restrict__ counts, double wq)
 {
     coef_block<Tt, T, RESP>(blockIdx.x, nodes, gd, ev0, evs, units, dirs, zen1, az1, fs, fallback_rel, singular_rel,
-                            M, counts, wq, skip, skip_stride);
+                            M, counts, wq, nullptr);
 }
 
 // A scan's spectra and coefficients, which depend on nothing of each other, in
@@ -685,7 +684,7 @@ __global__ __launch_bounds__(N / 8) void k_spectrum_coef(const Tin* __restrict__
                                                 nullptr);
     else
         coef_block<Tt, T, false, N / 8>(blockIdx.x - spec_blocks, nodes, gd, ev0, nullptr, nullptr, dirs, zen1, az1, fs,
-                                        fallback_rel, singular_rel, M, counts, 0.0, nullptr, 0);
+                                        fallback_rel, singular_rel, M, counts, 0.0, nullptr);
 }
 
 // E-field traces of one (event, direction, station range) per block; each
@@ -2906,12 +2905,11 @@ extern "C" au_status au_workspace_bytes(const au_table* tb, const au_event* ev, 
 template <typename Tt, typename T>
 static void launch_coef(hipStream_t st, const au_table* tb, const EvDesc& ev0, const EvDesc* evs,
                         const int2* units, int n_units, const double* dirs, double zen, double az,
-                        int64_t fs, double fb, double sg, MBin<T>* M, unsigned long long* counts,
-                        const int* skip = nullptr, int skip_stride = 0)
+                        int64_t fs, double fb, double sg, MBin<T>* M, unsigned long long* counts)
 {
     hipLaunchKernelGGL((k_coef<Tt, T, false>), dim3(n_units), dim3(kBlock), 0, st,
                        (const C2<Tt>*)tb->d_nodes, tb->g, ev0, evs, units, dirs, zen, az, fs, fb, sg,
-                       M, counts, 0.0, skip, skip_stride);
+                       M, counts, 0.0);
 }
 
 // k_spectrum_coef at N samples; false where the spectra take another kernel.
@@ -3344,7 +3342,7 @@ static au_status pattern_response(const au_table* tb, const au_event* ev, int32_
 #define RESP_(TT, T)                                                                        \
     hipLaunchKernelGGL((k_coef<TT, T, true>), dim3(n_dir), dim3(kBlock), 0, st,            \
                        (const C2<TT>*)tb->d_nodes, tb->g, ev0, nullptr, nullptr, dirs, 0.0, 0.0, \
-                       ev->fs_hz, 0.0, 0.0, (MBin<T>*)d_resp, nullptr, wq, nullptr, 0)
+                       ev->fs_hz, 0.0, 0.0, (MBin<T>*)d_resp, nullptr, wq)
     if (f64)
         RESP_(double, double);
     else if (tb->dtype == AU_F64)
@@ -4608,7 +4606,7 @@ __global__ __launch_bounds__(kBlock) void k_recon_step_coef(int it, int S, doubl
     __syncthreads();
     // (rows and directions of event e: direction e of the one descriptor)
     coef_block<Tt, T, false>(e, nodes, gd, ev0, nullptr, nullptr, cur, 0.0, 0.0, fs, fallback_rel, singular_rel, M,
-                             nullptr, 0.0, state + 4 * e, 0);
+                             nullptr, 0.0, state + 4 * e);
 }
 
 // ---------------------------------------------------------------------------
