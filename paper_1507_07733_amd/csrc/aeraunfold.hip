@@ -661,8 +661,12 @@ __global__ __launch_bounds__(kBlock) void k_coef(const C2<Tt>* __restrict__ node
                                                  const double* __restrict__ dirs, double zen1,
                                                  double az1, int64_t fs, double fallback_rel,
                                                  double singular_rel, MBin<T>* __restrict__ M,
-                                                 unsigned long long* __restrict__ counts, double wq)
+                                                 unsigned long long* __restrict__ counts, double wq,
+                                                 unsigned* __restrict__ tickets)
 {
+    // the work counters of the plan's next launch, cleared here: a launch of
+    // its own for them took 4.7 us per trace-length class
+    if (tickets != nullptr && blockIdx.x == 0 && threadIdx.x < 8) tickets[threadIdx.x] = 0u;
     coef_block<Tt, T, RESP>(blockIdx.x, nodes, gd, ev0, evs, units, dirs, zen1, az1, fs, fallback_rel, singular_rel,
                             M, counts, wq, nullptr);
 }
@@ -2220,12 +2224,6 @@ __global__ __launch_bounds__(N / 8) __attribute__((amdgpu_waves_per_eu(env_peaks
     }
 }
 
-__global__ void k_zero_u32(unsigned int* p, int n)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0u;
-}
-
 // ---------------------------------------------------------------------------
 // launch dispatch over N (compile-time FFT sizes)
 // ---------------------------------------------------------------------------
@@ -2426,7 +2424,6 @@ static hipError_t launch_fused(int n, hipStream_t st, const Tin* volt, const EvD
                                unsigned int* counter, const int* xcd_off)
 {
     if (n_units <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, st, counter, 8);
     switch (n) {
 #define F_(NN)                                                                                                  \
     case NN: {                                                                                                  \
@@ -2479,7 +2476,6 @@ static hipError_t launch_unfold_nv(hipStream_t st, const EvDesc& ev0, const EvDe
         if (share != nullptr) {
             grid = persistent_blocks;
         } else if (counter != nullptr) {
-            hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, st, counter, 8);
             grid = std::min(n_units, persistent_blocks);
         } else {
             // no more blocks than the device holds at once: each loops over
@@ -2905,11 +2901,12 @@ extern "C" au_status au_workspace_bytes(const au_table* tb, const au_event* ev, 
 template <typename Tt, typename T>
 static void launch_coef(hipStream_t st, const au_table* tb, const EvDesc& ev0, const EvDesc* evs,
                         const int2* units, int n_units, const double* dirs, double zen, double az,
-                        int64_t fs, double fb, double sg, MBin<T>* M, unsigned long long* counts)
+                        int64_t fs, double fb, double sg, MBin<T>* M, unsigned long long* counts,
+                        unsigned* tickets = nullptr)
 {
     hipLaunchKernelGGL((k_coef<Tt, T, false>), dim3(n_units), dim3(kBlock), 0, st,
                        (const C2<Tt>*)tb->d_nodes, tb->g, ev0, evs, units, dirs, zen, az, fs, fb, sg,
-                       M, counts, 0.0);
+                       M, counts, 0.0, tickets);
 }
 
 // k_spectrum_coef at N samples; false where the spectra take another kernel.
@@ -3342,7 +3339,7 @@ static au_status pattern_response(const au_table* tb, const au_event* ev, int32_
 #define RESP_(TT, T)                                                                        \
     hipLaunchKernelGGL((k_coef<TT, T, true>), dim3(n_dir), dim3(kBlock), 0, st,            \
                        (const C2<TT>*)tb->d_nodes, tb->g, ev0, nullptr, nullptr, dirs, 0.0, 0.0, \
-                       ev->fs_hz, 0.0, 0.0, (MBin<T>*)d_resp, nullptr, wq)
+                       ev->fs_hz, 0.0, 0.0, (MBin<T>*)d_resp, nullptr, wq, (unsigned*)nullptr)
     if (f64)
         RESP_(double, double);
     else if (tb->dtype == AU_F64)
@@ -3438,10 +3435,10 @@ static au_status enqueue_class_t(const au_table* tb, int tin, int64_t fs, double
             if (stage_events) HIP_TRY(hipEventRecord(stage_events[0], st));
             if (tb->dtype == AU_F64)
                 launch_coef<double, T>(st, tb, ev0, c.d_evs, c.d_cunits, c.n_cunits, dirs, 0, 0, fs, fb, sg, M,
-                                       (unsigned long long*)d_counts);
+                                       (unsigned long long*)d_counts, c.d_counter);
             else
                 launch_coef<float, T>(st, tb, ev0, c.d_evs, c.d_cunits, c.n_cunits, dirs, 0, 0, fs, fb, sg, M,
-                                      (unsigned long long*)d_counts);
+                                      (unsigned long long*)d_counts, c.d_counter);
             e = hipGetLastError();
             if (e != hipSuccess) return fail(AU_EDEVICE, std::string("k_coef: ") + hipGetErrorString(e));
             if (stage_events) HIP_TRY(hipEventRecord(stage_events[1], st));
@@ -3465,10 +3462,10 @@ static au_status enqueue_class_t(const au_table* tb, int tin, int64_t fs, double
     if (c.n_cunits > 0) {
         if (tb->dtype == AU_F64)
             launch_coef<double, T>(st, tb, ev0, c.d_evs, c.d_cunits, c.n_cunits, dirs, 0, 0, fs, fb, sg, M,
-                                   (unsigned long long*)d_counts);
+                                   (unsigned long long*)d_counts, c.d_counter);
         else
             launch_coef<float, T>(st, tb, ev0, c.d_evs, c.d_cunits, c.n_cunits, dirs, 0, 0, fs, fb, sg, M,
-                                  (unsigned long long*)d_counts);
+                                  (unsigned long long*)d_counts, c.d_counter);
         e = hipGetLastError();
         if (e != hipSuccess) return fail(AU_EDEVICE, std::string("k_coef: ") + hipGetErrorString(e));
     }

@@ -56,7 +56,7 @@ struct ClassLaunch {
     int n_cunits = 0;
     const int4* d_uunits = nullptr;  // (event, direction, station begin, end)
     int n_uunits = 0;
-    unsigned int* d_counter = nullptr;  // non-null: persistent unfold grid (8 counters)
+    unsigned int* d_counter = nullptr;  // non-null: persistent unfold grid (8 counters, cleared by k_coef)
     int persistent_blocks = 0;
     const int* d_share = nullptr;       // non-null: boundaries of the workgroups' shares of the units
     const int* d_xcd_off = nullptr;     // non-null: 8 per-XCD unit lists (9 boundaries)
