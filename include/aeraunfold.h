@@ -363,8 +363,9 @@ au_status au_pattern_response_quantized(const au_table* table, const au_event* e
  * run fused (section 4's
  * dual-domain container: the spectrum of a station is formed once and kept
  * on chip while every direction is unfolded from it): one kernel per class
- * takes units of (event, 16 stations, every direction), transforms each
- * station forward and unfolds all directions from the spectrum it keeps in
+ * takes units of (event, up to 8 stations, every direction -- or a part of the
+ * directions where stations are few), transforms each
+ * station forward and unfolds the directions from the spectrum it keeps in
  * registers, so no spectrum rows are written or read (and none allocated);
  * these classes always use a persistent grid.  The operations are those of
  * the separate stages; the results agree with them to rounding (the

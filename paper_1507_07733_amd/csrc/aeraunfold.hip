@@ -1179,11 +1179,11 @@ __device__ __forceinline__ R load_record(__amdgpu_buffer_rsrc_t r, unsigned j)
 // Events with at most this many directions take the fused kernel in batched
 // plans (their work units then cover every direction of a station range).
 constexpr int kFusedMaxDirs = 64;
-// Stations per work unit of the fused kernel.
+// Stations per work unit of the fused kernel, at most (cut_fused_units).
 constexpr int kFusedStations = 8;
 
-// One work unit (event, stations [s0, s1)) with ALL of the event's directions
-// per workgroup (persistent grid, units taken as in k_unfold).  Per station:
+// One work unit (event, directions [d0, d1) packed as d0 | d1 << 16, stations
+// [s0, s1)), mostly with ALL of the event's directions, per workgroup (persistent grid, units taken as in k_unfold).  Per station:
 //   1. its two channel traces (loaded ahead, after the previous station's
 //      last staging and before its last stores) go through the forward
 //      transform Z = F-(z), z = V_0 + i V_1, with the twiddles the inverse
@@ -1272,9 +1272,9 @@ __global__ __launch_bounds__(N / 8) __attribute__((amdgpu_waves_per_eu(4))) void
         if (t == 0) sh_u = next_unit();
         lds_barrier();
         const int un = __builtin_amdgcn_readfirstlane(sh_u);
-        const int4 wu = units[u];  // (event, -, first station, end station)
+        const int4 wu = units[u];  // (event, directions, first station, end station)
         const EvDesc ev = evs[wu.x];
-        const int s0 = wu.z, s1 = wu.w, D = ev.D;
+        const int s0 = wu.z, s1 = wu.w, d0 = wu.y & 0xffff, d1 = wu.y >> 16;
         const unsigned nb = (unsigned)ev.nb, k_lo = (unsigned)ev.k_lo;
         const MBin<T>* __restrict__ Me = M + ev.m_off;
         const Tin* __restrict__ Ve = volt + ev.volt_off;
@@ -1318,7 +1318,7 @@ __global__ __launch_bounds__(N / 8) __attribute__((amdgpu_waves_per_eu(4))) void
             fft_pp<T, N, E, -1, TW_LF, RMAX, false>(x, lb, la, tw, t, w, ltw);
             // the first direction's coefficients (issued after the previous
             // station's last stores, a transform and the split ago)
-            load_coef(0, pm);
+            load_coef(d0, pm);
             // 2. the in-band split of this thread's bins, through la (natural
             // order; gathered last before the transform's final exchange)
 #pragma unroll
@@ -1381,8 +1381,8 @@ __global__ __launch_bounds__(N / 8) __attribute__((amdgpu_waves_per_eu(4))) void
                     buffer_store_nt(x[i].im, r, toff, (int)((N + TT * i) * sizeof(T)));
                 }
             };
-            for (int d = 0; d + 1 < D; ++d) direction(d, false);
-            direction(D - 1, true);
+            for (int d = d0; d + 1 < d1; ++d) direction(d, false);
+            direction(d1 - 1, true);
         }
         __builtin_amdgcn_s_setprio(0);
         u = un;
@@ -2416,6 +2416,43 @@ static int fused_blocks()
 static bool fused_eligible(int prec, int n, int max_dirs, int max_nb)
 {
     return prec == AU_PREC_FP32 && (n == 2048 || n == 4096) && max_dirs <= kFusedMaxDirs && max_nb <= 2 * (n / 8);
+}
+
+// Workgroups of the fused kernel that the device holds at once.
+static int fused_resident(int tin, int n)
+{
+    return n == 2048 ? (tin == AU_F64 ? fused_blocks<double, 2048>() : fused_blocks<float, 2048>())
+                     : (tin == AU_F64 ? fused_blocks<double, 4096>() : fused_blocks<float, 4096>());
+}
+
+// The units of a fused class: 8 stations with every direction, stations halved
+// while there are fewer than two units per workgroup that the device holds, and
+// where even single stations are fewer than the workgroups, the directions shared
+// out (each part transforms its station again).  A unit is a serial chain of
+// stations x (directions + 1) transforms; with 8 stations whatever the class, a
+// plan of few events left most of the device idle for the longest chain's time.
+// Events of 3 to 124 stations, 8 stations -> this: 8 events x 64 directions x 2048
+// or 4096 samples 2430 -> 315 us, 6 x 16 579 -> 126, 40 x 30 1973 -> 588, 100 x
+// 16 1161 -> 626, 160 x 8 x 2048 460 -> 348; 160 x 16 x 4096 of 124 stations
+// keeps 8 (2640).  One unit per workgroup: 100 x 16 760, 40 x 30 666; four: 630, 588.
+static void cut_fused_units(const std::vector<EvDesc>& evs, int resident, std::vector<int4>& units)
+{
+    int64_t stations = 0;
+    for (const EvDesc& ev : evs) stations += ev.S;
+    auto count = [&](int per) {
+        int64_t n = 0;
+        for (const EvDesc& ev : evs) n += (ev.S + per - 1) / per;
+        return n;
+    };
+    int per = kFusedStations;
+    while (per > 1 && count(per) < 2 * (int64_t)resident) per /= 2;
+    const int parts = (int)std::max<int64_t>(1, per == 1 && stations > 0 ? resident / stations : 1);
+    for (int e = 0; e < (int)evs.size(); ++e) {
+        const int p = std::min(parts, evs[e].D), len = (evs[e].D + p - 1) / p;
+        for (int s0 = 0; s0 < evs[e].S; s0 += per)
+            for (int d0 = 0; d0 < evs[e].D; d0 += len)
+                units.push_back(int4{e, d0 | std::min(evs[e].D, d0 + len) << 16, s0, std::min(evs[e].S, s0 + per)});
+    }
 }
 
 template <typename Tin>
@@ -3699,10 +3736,7 @@ extern "C" au_status au_plan_create(const au_table* tb, const au_batch* b, au_pl
             const int ci = (int)c.evs.size();
             c.evs.push_back(descs[e]);
             if (c.fused) {
-                // units (event, -, station range) covering every direction
                 for (int d = 0; d < descs[e].D; ++d) c.cu.push_back(int2{ci, d});
-                for (int s0 = 0; s0 < descs[e].S; s0 += kFusedStations)
-                    c.uu.push_back(int4{ci, 0, s0, std::min(descs[e].S, s0 + kFusedStations)});
                 continue;
             }
             for (int st = 0; st < descs[e].S; ++st) c.su.push_back(int2{ci, st});
@@ -3718,6 +3752,7 @@ extern "C" au_status au_plan_create(const au_table* tb, const au_batch* b, au_pl
                     c.uu.push_back(int4{ci, d, s0, std::min(descs[e].S, s0 + cs)});
             }
         }
+        if (c.fused) cut_fused_units(c.evs, fused_resident(b->trace_dtype, n), c.uu);
         if ((b->flags & AU_PLAN_XCD) && !c.shared) {
             // all units of one event (its directions' station chunks) go to one
             // of 8 lists, the list with the least work so far (work =
