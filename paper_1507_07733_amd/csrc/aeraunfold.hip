@@ -4678,8 +4678,12 @@ __device__ __forceinline__ void env_store_trace(const C2<T> (&x)[8], int out0, u
 // direction's angular slice in LDS) and takes the coefficients of its own two
 // bins per thread from it, as k_event_fused does, then the envelope maxima of
 // its station as k_env_peaks, so that a pass is one launch with nothing between
-// it and the next.  Workgroup 0 writes the direction and the state (as
-// recon_step_block: [0] stop, [1] directions, [2] converged, [3] degenerate).
+// it and the next.  Workgroup 0 writes the direction and the state: [0] the
+// number, from 1, of the pass that stopped the loop (0: none has), [1] directions,
+// [2] converged, [3] degenerate.  The number lets every wave of a pass tell a stop
+// of an earlier pass, which all see alike, from its own, which workgroup 0 may be
+// writing as the others read: a wave that left on that one would be missing from
+// its workgroup's sums.
 // The coefficient row in M is written only for env_redo (by every workgroup that
 // needs it, the same values).  Needs a plane fit's kBlock threads (N >= 2048)
 // and at most kMaxSliceNodes frequency nodes in the band.
@@ -4704,7 +4708,10 @@ __global__ __launch_bounds__(N / 8) void k_recon_pass(int it, EvDesc ev, double 
     __shared__ unsigned top_key[3][1], near_cnt[3][1];
     const int t = threadIdx.x, s = blockIdx.x, S = ev.S;
     const unsigned nb = (unsigned)ev.nb, k_lo = (unsigned)ev.k_lo;
-    if (it > 0 && state[0]) return;
+    if (it > 0) {
+        const int stopped = state[0];
+        if (stopped != 0 && stopped <= it) return;
+    }
     // what the direction does not decide comes first
     QbTwiddles<T, N> q;
     qb_load_uniform<T, N>(q, tw, t);
@@ -4721,7 +4728,7 @@ __global__ __launch_bounds__(N / 8) void k_recon_pass(int it, EvDesc ev, double 
         for (int k = t; k < S; k += TT) changed |= row[k] != row[k - S];
         if (!__syncthreads_or(changed)) {
             if (s == 0 && t == 0) {
-                state[0] = 1;
+                state[0] = it + 1;
                 state[2] = 1;
             }
             return;
@@ -4731,7 +4738,8 @@ __global__ __launch_bounds__(N / 8) void k_recon_pass(int it, EvDesc ev, double 
     const bool ok = plane_direction(S, dt_ns, pos, row, zen, az);
     if (s == 0 && t == 0) {
         if (it == 0) state[2] = 0;
-        state[0] = state[3] = ok ? 0 : 1;
+        state[0] = ok ? 0 : it + 1;
+        state[3] = ok ? 0 : 1;
         state[1] = it + (ok ? 1 : 0);
         if (ok) {
             dirs[2 * it] = zen;
