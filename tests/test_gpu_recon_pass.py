@@ -1,14 +1,17 @@
 """The one-event loop at 2048 and 4096 samples, a launch per pass (a workgroup per station, up to 1024 stations): kept
 traces and maxima after convergence with more stations than the device holds workgroups, and on both sides of the
-1024 stations.  Against the batched loop (the same directions and times to the bit) and the single-direction call for
-the kept traces."""
+1024 stations; passes that go out in several chunks and a loop that ends unconverged, or after one pass; and times
+that ties decide.  Against the batched loop (the same directions and times to the bit), the oracle, and the
+single-direction call for the kept traces."""
 import numpy as np
 import pytest
 
+from oracle import oracle as O
 from paper_1507_07733_amd import synth as S
 
-from helpers import TOL_FP32, TOL_FP64, assert_close
+from helpers import TOL_FP32, TOL_FP64, assert_close, oracle_unfold
 from test_gpu_envelope import api  # noqa: F401
+from test_gpu_reconstruct import check_passes
 
 pytestmark = pytest.mark.gpu
 G = S.GRID_COARSE
@@ -55,4 +58,52 @@ def test_kept_traces_after_convergence(api, s, n, prec):  # noqa: F811
         rec = api.reconstruct(tab, ev, v, pos, max_iter=12, efield=out)
         assert rec.converged
         equals_batch(api, tab, ev, v, pos, rec, 12)
+        kept_results(api, tab, ev, v, rec, prec == 32)
+
+
+@pytest.mark.parametrize("prec", [64, 32])
+@pytest.mark.parametrize("n", [2048, 4096])
+@pytest.mark.parametrize("max_iter", [1, 2, 6, 7])
+def test_loop_that_does_not_converge(api, n, max_iter, prec):  # noqa: F811
+    """Noise: every pass the oracle's (double); single precision against the batched loop and the oracle's envelopes."""
+    print("[case] recon pass noise N", n, "max_iter", max_iter, "prec", prec, flush=True)
+    t = S.pattern_table(G, cfg=0)
+    pos = S.station_positions(12, area_km2=6.0 * 12 / 124)
+    volt = S.traces(12, n, cfg=0, event=900)
+    tab, ev, v = setup(api, prec, t, volt)
+    rec = api.reconstruct(tab, ev, v, pos, max_iter=max_iter, efield=True)
+    equals_batch(api, tab, ev, v, pos, rec, max_iter)
+    kept_results(api, tab, ev, v, rec, prec == 32)
+    if prec == 64:
+        dirs, times, conv = O.reconstruct(G, t, volt, pos, S.FS_HZ, S.BAND_LO_HZ, S.BAND_HI_HZ, max_iter=max_iter)
+        assert len(dirs) == max_iter and not conv  # the case this test is for
+        assert not rec.converged and np.array_equal(rec.times, times)
+        assert np.max(np.abs(rec.dirs - dirs)) < 1e-9
+    else:
+        t, volt = t.astype(np.complex64), volt.astype(np.float32)
+        check_passes(G, t, volt, pos, rec, TOL_FP32)
+        ref, _, _ = oracle_unfold(G, t, volt, rec.direction[None, :])
+        assert_close(rec.efield.cpu().numpy(), ref[0], True, "kept traces against the oracle")
+
+
+@pytest.mark.parametrize("prec", [64, 32])
+@pytest.mark.parametrize("n", [2048, 4096])
+def test_times_decided_by_ties(api, n, prec):  # noqa: F811
+    """Every station tied (traces of half the period), one station without a signal, one bin (a constant envelope), and
+    a band from 0 Hz: the maxima that are evaluated again, each workgroup writing the coefficients it needs."""
+    print("[case] recon pass ties N", n, "prec", prec, flush=True)
+    s = 40
+    pos = S.station_positions(s)
+    volt, _ = S.plane_wave_traces(pos, n, 15.0, 200.0, cfg=6, event=n)
+    half = volt.copy()
+    half[..., n // 2:] = half[..., :n // 2]
+    dead = volt.copy()
+    dead[7] = 0.0
+    pattern, ident = S.pattern_table(G, cfg=0), S.identity_table(G)
+    for table, x, band in ((pattern, half, {}), (pattern, dead, {}),
+                           (ident, volt, dict(band_lo_hz=50_000_000, band_hi_hz=50_000_000)),
+                           (ident, volt + 3.0, dict(band_lo_hz=0, band_hi_hz=40_000_000))):
+        tab, ev, v = setup(api, prec, table, x, **band)
+        rec = api.reconstruct(tab, ev, v, pos, max_iter=4, efield=True)
+        equals_batch(api, tab, ev, v, pos, rec, 4)
         kept_results(api, tab, ev, v, rec, prec == 32)
