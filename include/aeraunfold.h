@@ -406,7 +406,10 @@ au_status au_plan_run(au_plan* plan, const void* d_volt, void* d_efield, void* s
  * ([n_classes][variant count], nullable) receives the average ms per launch
  * (-1 for a variant not built for that length), best ([n_classes], nullable)
  * the chosen variant.  Synchronises the stream.  The global per-length
- * choice (au_set_unfold_variant) is left unchanged.
+ * choice (au_set_unfold_variant) is left unchanged.  In FP64 the work lists of a
+ * shape are cut when it is first tried and kept until the plan is freed (a few
+ * MB at most): runs in flight on other streams, and graphs that a program has
+ * captured runs into, keep the shape and the lists they were launched with.
  */
 au_status au_plan_autotune(au_plan* plan, const void* d_volt, void* d_efield, int32_t reps, void* stream,
                            double* ms, int32_t* best);

@@ -3426,6 +3426,14 @@ struct ClassPlan {
     // FP64: the unfold's units in equal shares, one per workgroup (plan_shares)
     std::vector<int2> ev_sd;  // stations and directions of each event
     int* d_share = nullptr;
+    // the shares cut so far, by the stations a workgroup takes side by side and the
+    // workgroups: what a launch was given stays as it was until the plan is freed
+    struct Shares {
+        int G, blocks, shares, n_units;
+        int4* d_units;
+        int* d_share;
+    };
+    std::vector<Shares> cut;
 };
 
 struct au_plan {
@@ -3435,6 +3443,7 @@ struct au_plan {
     int64_t fs = 0;
     double fb = 0, sg = 0;
     void* d_mem = nullptr;
+    std::vector<void*> d_cut;  // shares of shapes tried by au_plan_autotune (a few per class at most)
     void* d_x = nullptr;
     void* d_m = nullptr;
     double* d_dirs = nullptr;
@@ -3580,17 +3589,16 @@ constexpr int kMaxShares = 256 * 32;
 constexpr int kPieceStations = 32;
 
 // Cuts an FP64 class's (event, direction) rows into the units of equal shares, one
-// per workgroup that the device holds of the class's unfold shape, and copies units
-// and boundaries to the device (synchronous; nothing of the class may be running).
+// per workgroup that the device holds of the class's unfold shape: units, and each
+// share's first unit.
 // Work is counted in rounds of the stations a workgroup takes side by side.  A
 // share is one piece of each of `turns` equal parts of the list, so that the
 // workgroups write one region together (one piece per share: 3 % slower).  With
 // xcd the list is cut into eighths first, for the workgroups b of equal b mod 8:
 // these run on one XCD, whose L2 then fetches an event's spectrum rows, and each
 // direction's coefficient row, alone.
-static hipError_t plan_shares(ClassPlan& c, bool xcd)
+static void plan_shares(const ClassPlan& c, bool xcd, int G, std::vector<int4>& units, std::vector<int>& share)
 {
-    const int G = unfold_stations<double>(c.N, c.variant);
     int64_t total = 0;
     for (const int2& e : c.ev_sd) total += (int64_t)((e.x + G - 1) / G) * e.y;
     // a multiple of 8; an empty share does no harm
@@ -3619,9 +3627,8 @@ static hipError_t plan_shares(ClassPlan& c, bool xcd)
     }
     first.resize((size_t)pieces + 1, (int)list.size());
     // workgroup by workgroup
-    std::vector<int4> units;
-    std::vector<int> share(1, 0);
     units.reserve(list.size());
+    share.assign(1, 0);
     for (int b = 0; b < shares; ++b) {
         const int64_t l = b % lists, i = b / lists;
         for (int64_t k = 0; k < turns; ++k) {
@@ -3630,11 +3637,47 @@ static hipError_t plan_shares(ClassPlan& c, bool xcd)
         }
         share.push_back((int)units.size());
     }
-    c.n_uunits = (int)units.size();
-    c.persistent_blocks = shares;
-    hipError_t e = hipMemcpy(c.d_uunits, units.data(), units.size() * sizeof(int4), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(c.d_share, share.data(), share.size() * sizeof(int), hipMemcpyHostToDevice);
-    return e;
+}
+
+// Gives a class the shares of its unfold shape (c.variant, c.persistent_blocks).  The
+// first ones go into the plan's memory at c.d_uunits and c.d_share; others are
+// cut once each into memory of their own, so that a run still in flight and a
+// program's captured graph keep the lists that they were launched with.
+static hipError_t set_shares(au_plan* pl, ClassPlan& c)
+{
+    const int G = unfold_stations<double>(c.N, c.variant);
+    for (const ClassPlan::Shares& k : c.cut) {
+        if (k.G != G || k.blocks != c.persistent_blocks) continue;
+        c.d_uunits = k.d_units;
+        c.d_share = k.d_share;
+        c.n_uunits = k.n_units;
+        c.persistent_blocks = k.shares;
+        return hipSuccess;
+    }
+    std::vector<int4> units;
+    std::vector<int> share;
+    plan_shares(c, (pl->flags & AU_PLAN_XCD) != 0, G, units, share);
+    const size_t ub = units.size() * sizeof(int4), sb = share.size() * sizeof(int);
+    int4* d_units = c.d_uunits;
+    int* d_share = c.d_share;
+    if (!c.cut.empty()) {
+        void* mem = nullptr;
+        const hipError_t e = hipMalloc(&mem, ub + sb);
+        if (e != hipSuccess) return e;
+        pl->d_cut.push_back(mem);
+        d_units = (int4*)mem;
+        d_share = (int*)((unsigned char*)mem + ub);
+    }
+    hipError_t e = hipMemcpy(d_units, units.data(), ub, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(d_share, share.data(), sb, hipMemcpyHostToDevice);
+    if (e != hipSuccess) return e;
+    const ClassPlan::Shares k{G, c.persistent_blocks, (int)share.size() - 1, (int)units.size(), d_units, d_share};
+    c.cut.push_back(k);
+    c.d_uunits = d_units;
+    c.d_share = d_share;
+    c.n_uunits = k.n_units;
+    c.persistent_blocks = k.shares;
+    return hipSuccess;
 }
 
 extern "C" au_status au_plan_free(au_plan* pl)
@@ -3644,6 +3687,7 @@ extern "C" au_status au_plan_free(au_plan* pl)
     if (pl->graph) (void)hipGraphDestroy(pl->graph);
     if (pl->cap_stream) (void)hipStreamDestroy(pl->cap_stream);
     if (pl->d_mem) (void)hipFree(pl->d_mem);
+    for (void* m : pl->d_cut) (void)hipFree(m);
     for (hipEvent_t e : pl->ev) (void)hipEventDestroy(e);
     delete pl;
     return AU_OK;
@@ -3872,7 +3916,7 @@ extern "C" au_status au_plan_create(const au_table* tb, const au_batch* b, au_pl
         if (hc[i].shared) {
             c.d_share = (int*)(base + co[i].share);
             for (const EvDesc& d : hc[i].evs) c.ev_sd.push_back(int2{d.S, d.D});
-            PLAN_TRY(plan_shares(c, (b->flags & AU_PLAN_XCD) != 0));
+            PLAN_TRY(set_shares(pl, c));
         }
         pl->classes.push_back(c);
     }
@@ -3976,16 +4020,14 @@ extern "C" au_status au_plan_autotune(au_plan* pl, const void* d_volt, void* d_e
     HIP_TRY(hipGetDevice(&dev));
     if (dev != pl->device) return fail(AU_EINVAL, "plan lives on another device");
     hipStream_t st = (hipStream_t)stream;
-    // another unfold shape, and its shares of the units (the stream is idle: each
-    // timed run has been waited for)
+    // another unfold shape, and its shares of the units
     auto set_variant = [&](ClassPlan& cp, int v) {
         cp.variant = v;
         cp.persistent_blocks = au::persistent_blocks(pl->prec, cp.N, v, pl->device);
         if (cp.d_share == nullptr) return AU_OK;
-        const hipError_t e = plan_shares(cp, (pl->flags & AU_PLAN_XCD) != 0);
+        const hipError_t e = set_shares(pl, cp);
         return e == hipSuccess ? AU_OK : fail(AU_EDEVICE, std::string("work shares: ") + hipGetErrorString(e));
     };
-    HIP_TRY(hipStreamSynchronize(st));
     const bool was_timing = pl->timing;
     const std::vector<double> saved_ms = pl->stage_ms;
     const uint64_t saved_runs = pl->timed_runs;
