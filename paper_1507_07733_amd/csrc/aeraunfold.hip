@@ -4380,16 +4380,28 @@ static int env_peaks_blocks()
     return blocks;
 }
 
+// Whether a band of nb bins is so narrow that the samples next to an envelope's
+// maximum come within rounding of it, so that k_env_peaks would evaluate most
+// stations a second time: the envelope of nb bins falls by some (nb / n)^2 from one
+// sample to the next, which has to stand out of kEnvNear (float) or of a step of the
+// keys, 2^-20 (double).  Scans of 124 stations x 512 directions, k_unfold_env against
+// k_env_peaks: float, 4096 samples, 8 bins 741 and 2749 us, 32 bins 744 and 874, 51
+// bins 745 and 658; 2048, 32 bins 327 and 356, 43 bins 328 and 329; double, 4096, 11
+// bins 1663 and 2593, 16 bins 1664 and 1652; 2048, 5 bins 800 and 1058, 8 bins 803 and
+// 764.
+static bool narrow_band(bool f32, int n, int nb) { return (int64_t)nb * (f32 ? 48 : 256) < n; }
+
 // Whether the envelope peaks of n-sample traces whose largest band is nb bins
 // come from k_env_peaks: it takes a wavefront per 512 samples and bands of at
-// most a quarter of the samples (30-80 MHz at 200 MHz sampling is that).  In
+// most a quarter of the samples (30-80 MHz at 200 MHz sampling is that), and not
+// narrow ones.  In
 // float, whose peaks differ from k_unfold_env's in the last digits, not for
 // the direction fit (scores: sums of their squares in double, which a change of
 // kernel would move beyond double's digits) nor, so that fit and scan agree
 // where they are held to each other that closely, for 1024-sample scans.
 static bool env_peaks_applies(bool f32, int n, int nb, bool scores)
 {
-    if (n < 512 || nb > n / 4) return false;
+    if (n < 512 || nb > n / 4 || narrow_band(f32, n, nb)) return false;
     return !(f32 && (scores || n == 1024));
 }
 
@@ -4929,12 +4941,16 @@ au_status check_recon(const au_table* tb, const au_event* ev, int32_t max_iter, 
 
 // Whether the loop of one event runs as one launch per pass (k_recon_pass): 2048
 // or 4096 samples (the plane fit's threads), a band of at most a quarter of
-// them (k_env_peaks's transform) within the frequency nodes LDS holds, and at
+// them (k_env_peaks's transform) and at least a sixteenth (below, one of a hundred
+// stations evaluated a second time is usual, and the pass waits for it; 124 stations,
+// two passes, launches apart and one a pass: double, 4096 samples, N/32 bins 96 and
+// 112 us, N/24 96 and 86; float, 4096, N/24 86 and 94, N/16 88 and 77), within the
+// frequency nodes LDS holds, and at
 // most four stations per CU of the smallest part, beyond which the step that
 // every workgroup repeats (about 6 us) costs more than the launches it saves.
 static bool recon_pass_applies(const au_table* tb, const au_event* ev, const EvParams& p)
 {
-    if ((p.N != 2048 && p.N != 4096) || p.nb > p.N / 4 || p.S > 1024) return false;
+    if ((p.N != 2048 && p.N != 4096) || p.nb > p.N / 4 || p.nb < p.N / 16 || p.S > 1024) return false;
     return band_in_slice(tb->g, p, ev->fs_hz);
 }
 
