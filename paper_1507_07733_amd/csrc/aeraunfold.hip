@@ -4767,7 +4767,7 @@ __device__ __forceinline__ void env_store_trace(const C2<T> (&x)[8], int out0, u
 }
 
 // Pass `it` (times hist row `it` -> direction `it` -> times row it + 1) of the
-// loop of an event of up to a few stations per CU, bound by latency: a chain of
+// loop of an event of up to a station or two per CU, bound by latency: a chain of
 // launches that each work for a few microseconds.  Every workgroup repeats the
 // step (the convergence test of rows it - 1 and it, the plane fit, the
 // direction's angular slice in LDS) and takes the coefficients of its own two
@@ -4945,12 +4945,17 @@ au_status check_recon(const au_table* tb, const au_event* ev, int32_t max_iter, 
 // stations evaluated a second time is usual, and the pass waits for it; 124 stations,
 // two passes, launches apart and one a pass: double, 4096 samples, N/32 bins 96 and
 // 112 us, N/24 96 and 86; float, 4096, N/24 86 and 94, N/16 88 and 77), within the
-// frequency nodes LDS holds, and at
-// most four stations per CU of the smallest part, beyond which the step that
-// every workgroup repeats (about 6 us) costs more than the launches it saves.
+// frequency nodes LDS holds, and a station per CU, or two of the smallest workgroups
+// (float, 2048 samples): the step that every workgroup repeats is a chain of some 6
+// us, which a second round of workgroups adds to the pass, and more than one a CU
+// lengthen for each other.  Two passes, launches apart and one a pass: float, 4096
+// samples, 256 stations 79 and 67 us, 320 84 and 99, 640 116 and 144; 2048 samples, 512
+// stations 89 and 71, 640 93 and 108; double, 2048, 256 stations 74 and 66, 320 85 and
+// 93; 4096, 256 stations 92 and 81, 320 115 and 121.
 static bool recon_pass_applies(const au_table* tb, const au_event* ev, const EvParams& p)
 {
-    if ((p.N != 2048 && p.N != 4096) || p.nb > p.N / 4 || p.nb < p.N / 16 || p.S > 1024) return false;
+    if ((p.N != 2048 && p.N != 4096) || p.nb > p.N / 4 || p.nb < p.N / 16) return false;
+    if (p.S > (ev->prec == AU_PREC_FP32 && p.N == 2048 ? 512 : 256)) return false;
     return band_in_slice(tb->g, p, ev->fs_hz);
 }
 

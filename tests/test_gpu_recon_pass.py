@@ -1,8 +1,8 @@
-"""The one-event loop at 2048 and 4096 samples, a launch per pass (a workgroup per station, up to 1024 stations): kept
-traces and maxima after convergence with more stations than the device holds workgroups, and on both sides of the
-1024 stations; passes that go out in several chunks and a loop that ends unconverged, or after one pass; and times
-that ties decide.  Against the batched loop (the same directions and times to the bit), the oracle, and the
-single-direction call for the kept traces."""
+"""The one-event loop at 2048 and 4096 samples, a launch per pass (a workgroup per station, up to 256 stations, or 512
+in single precision at 2048 samples): kept traces and maxima after convergence on both sides of these numbers; passes
+that go out in several chunks and a loop that ends unconverged, or after one pass; and times that ties decide.  Against
+the batched loop (the same directions and times to the bit), the oracle, and the single-direction call for the kept
+traces."""
 import numpy as np
 import pytest
 
@@ -45,7 +45,8 @@ def kept_results(api, tab, ev, v, rec, f32):
 
 
 @pytest.mark.parametrize("prec", [64, 32])
-@pytest.mark.parametrize("s,n", [(40, 4096), (700, 2048), (1024, 2048), (1025, 2048), (1024, 4096)])
+@pytest.mark.parametrize("s,n", [(40, 4096), (256, 2048), (257, 2048), (256, 4096), (257, 4096), (512, 2048), (513, 2048),
+                                 (1024, 4096)])
 def test_kept_traces_after_convergence(api, s, n, prec):  # noqa: F811
     import torch
     print("[case] recon pass S", s, "N", n, "prec", prec, flush=True)
