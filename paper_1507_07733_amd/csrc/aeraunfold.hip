@@ -3022,15 +3022,20 @@ static bool launch_spectrum_coef_t(hipStream_t st, const au_table* tb, const au_
 }
 
 // The spectra of one event's stations and the coefficients of its ev0.D
-// directions (dirs, or with null the one direction zen, az).  In one launch
-// while the directions' workgroups fit the device at once (256 of 4096 samples,
-// twice as many of half the length): a launch costs 4 to 5 us and neither half
-// fills the device.  Above, the coefficients are better off in k_coef's smaller
-// workgroups.  Scan, apart -> in one launch: FP32 61 stations x 2048 samples x 64
+// directions (dirs, or with null the one direction zen, az).  In one launch while
+// there are few directions: a launch costs 4 to 5 us and neither half fills the
+// device.  Above, the coefficients are better off in k_coef's smaller workgroups.
+// The lines (in directions x samples) lie where no scan measured slower by more than
+// 2 us: in float 2^20, in double, whose workgroups take twice the LDS, three
+// quarters of it.  Scan, apart -> in one launch: FP32 61 stations x 2048 samples x 64
 // directions 29.5 -> 25.5 us, 61 x 4096 x 64 47.2 -> 40.8, 33 x 1024 x 256 34.9 ->
-// 31.8, 10 x 512 x 40 20.3 -> 18.3; FP64 20 x 4096 x 16 34.2 -> 26.4, 5 x 4096 x
-// 256 42.9 -> 43.1, 5 x 4096 x 512 65.0 -> 67.0.
-constexpr int64_t kSpecCoefWork = 256 * 4096;  // directions x samples
+// 31.8, 10 x 512 x 40 20.3 -> 18.3; at the line 5 x 4096 x 256 35.9 -> 29.6, 124 x
+// 4096 x 256 249.3 -> 247.5, 124 x 1024 x 1024 256.2 -> 257.4; FP64 20 x 4096 x 16
+// 34.2 -> 26.4, at the line 5 x 2048 x 384 44.6 -> 38.9, 124 x 4096 x 192 355.8 ->
+// 352.5, 5 x 512 x 1536 74.3 -> 76.3; at 2^20 5 x 2048 x 512 39.6 -> 42.8, 5 x 4096 x
+// 256 42.7 -> 43.4, 124 x 4096 x 256 462.7 -> 458.7.
+template <typename T>
+constexpr int64_t spec_coef_work() { return (sizeof(T) == 4 ? 4 : 3) << 18; }
 template <typename T>
 static au_status spectrum_and_coef(hipStream_t st, const au_table* tb, const au_event* ev, const EvDesc& ev0,
                                    const void* volt, const double* dirs, double zen, double az, XBin<T>* X, MBin<T>* M,
@@ -3038,7 +3043,7 @@ static au_status spectrum_and_coef(hipStream_t st, const au_table* tb, const au_
 {
     const bool tin64 = ev->trace_dtype == AU_F64, tab64 = tb->dtype == AU_F64;
     bool done = false;
-    if ((int64_t)ev0.D * ev0.N <= kSpecCoefWork)
+    if ((int64_t)ev0.D * ev0.N <= spec_coef_work<T>())
         done = tin64 ? (tab64 ? launch_spectrum_coef_t<double, double, T>(st, tb, ev, ev0, volt, dirs, zen, az, X, M, tw, counts)
                               : launch_spectrum_coef_t<double, float, T>(st, tb, ev, ev0, volt, dirs, zen, az, X, M, tw, counts))
                      : (tab64 ? launch_spectrum_coef_t<float, double, T>(st, tb, ev, ev0, volt, dirs, zen, az, X, M, tw, counts)
