@@ -287,7 +287,10 @@ au_status au_reconstruct_batch(const au_table* table, const au_event* ev, int32_
  * score is the inconsistency of those times with a plane wave from d,
  *   chi2(d) = min over t0 of sum_s (t_s(d) dt - t0 - tau_s(d))^2   [ns^2],
  *   tau_s(d) = -(n(d) . x_s) / c,  n(d) = (sin z cos a, sin z sin a),
- * with dt = 1e9 / fs ns, c = 0.299792458 m/ns; also power(d) = sum_s peak_s^2.
+ * with dt = 1e9 / fs ns, c = 0.299792458 m/ns; also power(d) = sum_s peak_s^2,
+ * summed in double.  The times are the scan's; so are the peaks, except in FP32
+ * from 2048 samples up, where they are evaluated another way and agree with the
+ * scan's (d_efield null) to single rounding only.
  * The best candidate minimises chi2 (the first on ties).  Then `levels`
  * refinements, all on the device with no host round trip: level l scores the
  * k x k grid around the previous best at spacing (step_zen, step_az) / 2^l,

@@ -4399,15 +4399,18 @@ static bool narrow_band(bool f32, int n, int nb) { return (int64_t)nb * (f32 ? 4
 // Whether the envelope peaks of n-sample traces whose largest band is nb bins
 // come from k_env_peaks: it takes a wavefront per 512 samples and bands of at
 // most a quarter of the samples (30-80 MHz at 200 MHz sampling is that), and not
-// narrow ones.  In
-// float, whose peaks differ from k_unfold_env's in the last digits, not for
-// the direction fit (scores: sums of their squares in double, which a change of
-// kernel would move beyond double's digits) nor, so that fit and scan agree
-// where they are held to each other that closely, for 1024-sample scans.
+// narrow ones.  In float, whose maxima differ from k_unfold_env's in the last digit
+// (1.1 u rms; against 64 bits 7.2e-8 rms, k_unfold_env's 9.0e-8), a fit's power, a
+// sum of their squares in double, moves with the kernel by up to 7e-8.  Fits of 2048
+// samples and more, whose scores are kept and compared between versions to double's
+// digits, therefore stay with k_unfold_env, and agree with the scan's maxima to
+// single rounding; shorter ones take the scan's kernel and agree to double's.
+// (Float, 124 stations x 512 directions, k_unfold_env and k_env_peaks: 512 samples
+// 290 and 94 us, 1024 samples 235 and 158, 2048 367 and 320, 4096 834 and 639.)
 static bool env_peaks_applies(bool f32, int n, int nb, bool scores)
 {
     if (n < 512 || nb > n / 4 || narrow_band(f32, n, nb)) return false;
-    return !(f32 && (scores || n == 1024));
+    return !(f32 && scores && n >= 2048);
 }
 
 // Envelope peaks of n_su station-unfolds: one event's (sunits null; ev0.S
