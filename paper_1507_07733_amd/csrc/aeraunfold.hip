@@ -1872,19 +1872,26 @@ __global__ __launch_bounds__((N / E) > kBlock ? (N / E) : kBlock) void k_unfold_
 // pass's eight inputs vanish, and the two transforms follow each other through
 // one buffer, so that twice the workgroups fit a CU.
 //
-// The sample of the maximum has to be the one that k_unfold_env takes,
-// whatever the rounding of either: where another sample comes within kEnvNear
-// of it (below), the station is evaluated again with k_unfold_env's
-// operations (env_redo), which decide.  That is a few stations in 10^5 for
-// traces with noise, and every station of a field that is zero.
+// The sample of the maximum has to be the one that k_unfold_env takes: where
+// another sample comes within 2^kEnvNear of it (below), the station is evaluated
+// again with k_unfold_env's operations (env_redo), which decide.  That is a few
+// stations in 10^5 for traces with noise, and every station of a field that is
+// zero (whose result is known, env_known) or exactly periodic: 124 stations x 4096
+// samples x 512 directions of traces of half the period take 3380 us in float and
+// 6490 in double, k_unfold_env 830 and 1951.
 
-// Two samples may change places between the two evaluations within kEnvNear of
-// the total field's maximum in amplitude: 32 u, 2^-19 in float and 2^-48 in double
-// (u = 2^-24 or 2^-53).  Over 2 10^5 stations of 512 to 4096 samples in float,
-// noise and pulses, the evaluations of a maximum differed by 1.1 u (rms) and 6.1 u
-// at most, so that two samples within 32 u are twenty standard deviations away.
-// (At 128 u four times the stations are decided twice, each the last of its
-// launch for about 14 us.)
+// The distance in amplitude, to the total field's maximum, within which another
+// sample counts as near: 32 u (u = 2^-24 or 2^-53), as its binary exponent.  It rests
+// on observation.  The two evaluations of a maximum differed by 0.8 to 1.8 u (rms) and
+// 9.8 u at most, in float and in double, over 4 10^6 stations of 512 to 4096 samples: noise,
+// pulses, tones, chirps and swept sines of flat envelope, and a carrier 10^4 times its
+// noise, the worst.  Two samples can then approach each other by 19.6 u.  What rounding
+// could add up to at worst is larger (2 log2 N roundings of a transform's largest
+// values, four times over: 96 u at 4096 samples); at 128 u four times the stations
+// would be evaluated twice, each the last of its launch for about 14 us.
+template <typename T>
+constexpr int kEnvNear = sizeof(T) == 4 ? -19 : -48;
+
 // Squares below this are decided by env_redo too: they may have lost bits to
 // underflow.
 template <typename T>
@@ -1899,17 +1906,17 @@ __device__ __forceinline__ unsigned env_key(float v) { return __float_as_uint(v)
 __device__ __forceinline__ unsigned env_key(double v) { return (unsigned)__double2hiint(v); }
 
 // The smallest key that counts as near the key m of a component's largest
-// square, R2 the total's: an amplitude within kEnvNear R of sqrt(m) has a square
-// above m (1 - 2 kEnvNear R / sqrt(m)); a relative step of 2^-b moves a key by
+// square, R2 the total's: an amplitude within 2^kEnvNear R of sqrt(m) has a square
+// above m (1 - 2 2^kEnvNear R / sqrt(m)); a relative step of 2^-b moves a key by
 // at most 2^(B - b) (B one more than its mantissa bits), and R / sqrt(m) is 1 for
 // the total itself and below 2^((e + 1) / 2) for a difference of e in the binary
 // exponents.  (Float: 64 keys for the total, which one station in 10^4 or 10^5 has
-// another sample in; double, whose keys are coarser than kEnvNear: two.)
+// another sample in; double, whose keys are coarser than that: two.)
 template <typename T>
 __device__ __forceinline__ unsigned env_near_key(unsigned m, unsigned r2, bool total)
 {
     constexpr int MB = sizeof(T) == 4 ? 23 : 20;
-    constexpr int STEP = MB + 1 + 1 - (sizeof(T) == 4 ? 19 : 48);  // log2 of 2 kEnvNear 2^B
+    constexpr int STEP = MB + 1 + 1 + kEnvNear<T>;  // log2 of 2 2^kEnvNear 2^B
     const int h = STEP + (total ? 0 : ((int)(r2 >> MB) - (int)(m >> MB) + 2) >> 1);
     const unsigned d = h <= 0 ? 2u : (h >= 31 ? m : (1u << h) + 1u);
     return d >= m ? 0u : m - d;
@@ -4388,7 +4395,7 @@ static int env_peaks_blocks()
 // Whether a band of nb bins is so narrow that the samples next to an envelope's
 // maximum come within rounding of it, so that k_env_peaks would evaluate most
 // stations a second time: the envelope of nb bins falls by some (nb / n)^2 from one
-// sample to the next, which has to stand out of kEnvNear (float) or of a step of the
+// sample to the next, which has to stand out of 2^kEnvNear (float) or of a step of the
 // keys, 2^-20 (double).  Scans of 124 stations x 512 directions, k_unfold_env against
 // k_env_peaks: float, 4096 samples, 8 bins 741 and 2749 us, 32 bins 744 and 874, 51
 // bins 745 and 658; 2048, 32 bins 327 and 356, 43 bins 328 and 329; double, 4096, 11
