@@ -187,13 +187,15 @@ def _check(rc: int):
 
 def _stream_handle(stream):
     import torch
-    if stream is not None:
-        return C.c_void_p(stream.cuda_stream)
-    if torch.cuda.is_initialized():
-        # the same handle without the Stream object that torch.cuda.current_stream() makes
-        # (0.4 us a call instead of 2.8, of a single-event call's 9)
-        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if stream is None:
+        # the current stream's handle without the Stream object that torch.cuda.current_stream()
+        # makes (0.4 us a call instead of 2.8, of a single-event call's 9), where torch has these
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        device = getattr(torch._C, "_cuda_getDevice", None)
+        if raw is not None and device is not None and torch.cuda.is_initialized():
+            return C.c_void_p(raw(device()))
+        stream = torch.cuda.current_stream()
+    return C.c_void_p(stream.cuda_stream)
 
 
 def _ptr(t):
