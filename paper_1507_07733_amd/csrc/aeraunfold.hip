@@ -2146,12 +2146,13 @@ __device__ __forceinline__ void env_bins(const MBin<T> (&mb)[2], const XBin<T> (
 // rows by event, one band): the peaks of u go to rows 3 u, and an event whose
 // skip flag is set is passed over.
 //
-// Bound by VALU issue: about 610 instructions per wave and station in float
-// (468 of them the two transforms, at 3 per point and radix-2 level), of which
-// the SIMDs can take one per 4 cycles.  124 stations x 4096 samples, k_unfold_env
-// against this: float, 512 directions, 830 -> 661 us; double, 2048 directions,
-// 7.36 -> 4.1 ms; 2048 samples, 87 stations x 700 directions, 352 -> 322 us and
-// 782 -> 521 us.  Registers: double 128 (4 waves per SIMD, two workgroups per
+// Float is bound by VALU issue: at 4096 samples 738 instructions per wave and
+// station (468 of them the two transforms, at 3 per point and radix-2 level), of
+// which the SIMDs take one per 4 cycles, 97 % of the time; LDS 36 % busy, no bank
+// conflicts.  Double issues for 62 % of the time, at 3.2 waves per SIMD: bound by
+// latency as much as by issue.  124 stations x 512 directions, k_unfold_env
+// against this: 4096 samples in float 833 -> 634 us (840 -> 674 on another box), in
+// double 1954 -> 1124; 2048 samples 367 -> 316 and 818 -> 518.  Registers: double 128 (4 waves per SIMD, two workgroups per
 // CU at 4096 samples); float 80 (6 waves: 734 us at 4 waves, and 64 registers
 // spill), except at 512 samples, where 4 waves measured 8 % faster.
 template <typename T, int N>
@@ -2481,7 +2482,7 @@ static int fused_resident(int tin, int n)
 // plan of few events left most of the device idle for the longest chain's time.
 // Events of 3 to 124 stations, 8 stations -> this: 8 events x 64 directions x 2048
 // or 4096 samples 2430 -> 315 us, 6 x 16 579 -> 126, 40 x 30 1973 -> 588, 100 x
-// 16 1161 -> 626, 160 x 8 x 2048 460 -> 348; 160 x 16 x 4096 of 124 stations
+// 16 1161 -> 626, 160 x 8 x 2048 465 -> 361; 160 x 16 x 4096 of 124 stations
 // keeps 8 (2640).  One unit per workgroup: 100 x 16 760, 40 x 30 666; four: 630, 588.
 static void cut_fused_units(const std::vector<EvDesc>& evs, int resident, std::vector<int4>& units)
 {
@@ -3475,7 +3476,7 @@ struct ClassPlan {
     int* d_xcd_off = nullptr;
     int xcd_max_list = 0;
     int max_nb = 0;  // largest band of the class's events (bins)
-    bool fused = false;  // spectrum and unfold in k_unfold_fused (units: event, station range)
+    bool fused = false;  // spectrum and unfold in k_unfold_fused (units: event, directions, station range)
     // FP64: the unfold's units in equal shares, one per workgroup (plan_shares)
     std::vector<int2> ev_sd;  // stations and directions of each event
     int* d_share = nullptr;
@@ -4804,7 +4805,7 @@ __device__ __forceinline__ void env_store_trace(const C2<T> (&x)[8], int out0, u
 // The coefficient row in M is written only for env_redo (by every workgroup that
 // needs it, the same values).  Needs a plane fit's kBlock threads (N >= 2048)
 // and at most kMaxSliceNodes frequency nodes in the band.
-// 124 stations x 4096 samples in double, traces kept, two passes: 90 -> 75 us per
+// 124 stations x 4096 samples in double, traces kept, two passes: 90 -> 75 us a
 // call against three steps with coefficients (11 us each) and two envelope
 // launches (13 us); 21 us a pass.
 template <typename Tt, typename T, int N>
