@@ -87,7 +87,7 @@ def cgroup_cpu_quota():
 
 def cpu_threads():
     """Every host core this process may use: its CPU affinity, bounded by the cgroup's CPU quota
-    (a GPU machine grants each job a share of its cores)."""
+    (a job may be granted a share of its machine's cores)."""
     try:
         n = len(os.sched_getaffinity(0))
     except Exception:

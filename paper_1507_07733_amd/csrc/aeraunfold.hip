@@ -2151,10 +2151,10 @@ __device__ __forceinline__ void env_bins(const MBin<T> (&mb)[2], const XBin<T> (
 // which the SIMDs take one per 4 cycles, 97 % of the time; LDS 36 % busy, no bank
 // conflicts.  Double issues for 62 % of the time, at 3.2 waves per SIMD: bound by
 // latency as much as by issue.  124 stations x 512 directions, k_unfold_env
-// against this: 4096 samples in float 833 -> 634 us (840 -> 674 on another box), in
-// double 1954 -> 1124; 2048 samples 367 -> 316 and 818 -> 518.  Registers: double 128 (4 waves per SIMD, two workgroups per
-// CU at 4096 samples); float 80 (6 waves: 734 us at 4 waves, and 64 registers
-// spill), except at 512 samples, where 4 waves measured 8 % faster.
+// against this: 4096 samples in float 833 -> 634 us, in double 1954 -> 1124; 2048
+// samples 367 -> 316 and 818 -> 518.  Registers: double 128 (4 waves per SIMD, two
+// workgroups per CU at 4096 samples); float 80 (6 waves: 734 us at 4 waves, and 64
+// registers spill), except at 512 samples, where 4 waves measured 8 % faster.
 template <typename T, int N>
 constexpr int env_peaks_min_waves() { return sizeof(T) == 8 || N == 512 ? 4 : 6; }
 
